@@ -1,0 +1,46 @@
+"""GPU parity of the fp32 matrix-core kernels (attention and GEMM of fp32 models)
+at the edges of their tiles, against the oracle in float64.
+
+Attention: 32-query and 32-key tiles dealt to four waves, so segments of less
+than one tile, of exactly one, and with one to four tiles and a remainder; head
+dims of every rounding (16, 32, 64) with and without 16-byte rows.  Bound: scores
+stay below about 24 in magnitude, so a score is off by at most 24 * 2^-24 * (a few
+roundings) and a probability by that relatively; with |v| <= 5 and fp32 sums the
+output is within 1e-5.
+
+GEMM: 32-row and 64-column tiles, K steps of 64 in a ring of three: selections
+around one row tile, and D and MLP widths of one, three, five and eight K steps.
+"""
+import numpy as np
+import pytest
+
+import workloads as W
+
+torch = pytest.importorskip("torch")
+S = pytest.importorskip("paper_2511_18672_amd")
+
+from test_gpu_attention import check, rand  # noqa: E402
+from test_gpu_parity import check_end_to_end  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hd", [1, 10, 16, 20, 32, 33, 48, 64])
+def test_fp32_attention_edges(hd):
+    rng = np.random.default_rng(hd)
+    heads = 3
+    D = heads * hd
+    lq, lk = [1, 31, 32, 33, 130, 5, 64], [1, 31, 32, 33, 130, 257, 7]
+    cu_q, cu_k = (np.concatenate([[0], np.cumsum(v)]).astype(np.int32) for v in (lq, lk))
+    ld = (D + 7) // 8 * 8
+    q = rand(rng, int(cu_q[-1]), D, 0.5 if hd < 20 else 2.0 / np.sqrt(hd))
+    k, v = rand(rng, int(cu_k[-1]), D), rand(rng, int(cu_k[-1]), D)
+    check(q, k, v, heads, hd, cu_q, cu_k, dtype="f32", tag=f"fp32 hd{hd}", ldq=ld, ldkv=ld + 8)
+
+
+@pytest.mark.parametrize("D,heads,mlp,n", [(64, 1, 64, 1), (64, 4, 192, 31), (192, 3, 320, 33), (512, 8, 2048, 70)])
+def test_fp32_gemm_edges(D, heads, mlp, n):
+    model = W.ModelCfg(D=D, heads=heads, head_dim=D // heads, mlp=mlp, L=1, dtype="f32")
+    wl = W.custom(f"fp32_{D}_{n}", model, [W.Request(2, 16, 16)], [n / 128], [0.5], [2])
+    R = check_end_to_end(wl)
+    assert R.n_sel == n
