@@ -19,8 +19,14 @@ namespace sphinx {
 namespace {
 // ---------------------------------------------------------------------------
 // bf16 GEMM with direct global->LDS copies (global_load_lds_dwordx4).
-//  * Block tile 128x128x64, 4 waves in 2x2, each a 64x64 tile of 2x2
-//    v_mfma_f32_32x32x16_bf16; two workgroups per CU.
+//  * Block tile 128x128x64, 4 waves in 2x2, each a 64x64 tile of 4x4
+//    v_mfma_f32_16x16x32_bf16; two workgroups per CU.  That form draws less
+//    power than the 32x32x16 one at the same work (register-only loops on random
+//    operands run at 2050 against 1790 TFLOP/s), and long runs are power-limited;
+//    eight-wave tiles of small selections, bound by latency, take the 32x32x16
+//    form with its smaller number of instructions (QKV at M 1613: 16.5 us against
+//    17.5).  Both add the products of a row in ascending k and round alike
+//    (bit-identical on every shape measured).
 //  * Operand tiles are unpadded 128-byte rows (A rows, then W rows, of one
 //    64-wide K step); chunk c of row r sits at c ^ ((r >> 1) & 7), which spreads
 //    the 16 rows of one ds_read_b128 pass (same chunk) over all 64 LDS banks.
@@ -33,14 +39,14 @@ namespace {
 //    kept free of it: the K loop is unrolled over the ring, making every
 //    fragment address a loop-invariant base plus an immediate offset.
 //  * K steps live in a 2-slot ring.  The wait for the next step's copies and
-//    the workgroup barrier sit inside the last 16-deep k-step of the current
+//    the workgroup barrier sit inside the last k-step (16 or 32 deep) of the current
 //    one, so the next step's first fragments are read (and the following
 //    copies issued) while the last MFMAs of the current step run; inside a
 //    step each k-step's fragment reads are issued before the previous
 //    k-step's MFMAs.  Barriers carry no memory fence: each wave waits for its
 //    own copies (vmcnt) and LDS reads (lgkmcnt) first.
-//  * Every output starts at its bias and accumulates its k-steps of 16 in
-//    ascending k, whatever the tile shape, so all variants give bit-identical
+//  * Every output starts at its bias and accumulates its k-steps in ascending
+//    k, whatever the tile shape, so all variants give bit-identical
 //    results.
 //  * A 192-row variant (wave tiles 96x64, 80 KB of LDS, epilogue staged one
 //    wave row at a time) is launched where its smaller tile count packs into
@@ -61,7 +67,10 @@ template <int BM, int BN, int NS, int EH = 1, int NW = 4>
 struct DmaCfg {
   static constexpr int BK = 64;
   static constexpr int NT = 64 * NW, WGN = NW / 2;  // threads; waves along N
-  static constexpr int WM = BM / 2, WN = BN / WGN, TI = WM / 32, TJ = WN / 32;
+  // MF x MF output blocks per MFMA; LG lane groups share a row, KS k-steps
+  static constexpr int MF = NW == 8 ? 32 : 16, NQ = MF * MF / 256, LG = 64 / MF, KS = 8 / LG;
+  using Acc = std::conditional_t<MF == 32, f32x16, f32x4>;
+  static constexpr int WM = BM / 2, WN = BN / WGN, TI = WM / MF, TJ = WN / MF;
   static constexpr int STAGE = (BM + BN) * 128;     // bytes per K-step
   static constexpr int COPIES = (BM + BN) / 8 / NW; // copy instructions per wave per stage
   static constexpr int CLD = BN + 4;                // epilogue staging row (fp32)
@@ -100,7 +109,7 @@ __device__ __forceinline__ void gemm_dma_body(const bf16* __restrict__ A, const 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / C::WGN, wn = wave % C::WGN;
-  const int g = lane >> 5, r32 = lane & 31;
+  const int g = lane / C::MF, rf = lane % C::MF;
 
   // copy sources: instruction i of this wave fills rows 8q .. 8q+7 of the
   // stage (q = wave * COPIES + i; rows < BM are A rows, the rest W rows)
@@ -127,23 +136,23 @@ __device__ __forceinline__ void gemm_dma_body(const bf16* __restrict__ A, const 
     for (int i = 0; i < C::COPIES; ++i)
       lds_dma16_at(src[i] + kt * C::BK, voff[i], base + (wave * C::COPIES + i) * 1024);
   };
-  // fragment offsets inside a stage (k-step ks of 16)
-  int foff[4];
+  // fragment offsets inside a stage (one k-step per MFMA)
+  int foff[C::KS];
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) foff[ks] = r32 * 128 + (((2 * ks + g) ^ ((r32 >> 1) & 7)) << 4);
+  for (int ks = 0; ks < C::KS; ++ks) foff[ks] = rf * 128 + (((C::LG * ks + g) ^ ((rf >> 1) & 7)) << 4);
   const int a_row0 = wm * C::WM, b_row0 = BM + wn * C::WN;
 
   // acc[i][j] is the transposed output block: the MFMA takes the W fragment
-  // as its A operand, so lane l holds row a_row0 + 32 i + l%32 of the tile and,
-  // in registers 4q .. 4q+3, its four consecutive columns wn WN + 32 j + 8q +
-  // 4(l/32) .. +3.  The accumulators start at the bias of their column, so the
+  // as its A operand, so lane l holds row a_row0 + MF i + l%MF of the tile and,
+  // in registers 4q .. 4q+3, its four consecutive columns wn WN + MF j + 8q +
+  // 4(l/MF) .. +3.  The accumulators start at the bias of their column, so the
   // epilogue adds no bias.
-  f32x16 acc[C::TI][C::TJ];
+  typename C::Acc acc[C::TI][C::TJ];
 #pragma unroll
   for (int j = 0; j < C::TJ; ++j)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const bf16x4 b4 = *reinterpret_cast<const bf16x4*>(bias + n0 + wn * C::WN + j * 32 + 8 * q + 4 * g);
+    for (int q = 0; q < C::NQ; ++q) {
+      const bf16x4 b4 = *reinterpret_cast<const bf16x4*>(bias + n0 + wn * C::WN + j * C::MF + 8 * q + 4 * g);
 #pragma unroll
       for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -173,14 +182,14 @@ __device__ __forceinline__ void gemm_dma_body(const bf16* __restrict__ A, const 
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 
-  bf16x8 fa[4][C::TI], fb[4][C::TJ];  // one register set per k-step
+  bf16x8 fa[C::KS][C::TI], fb[C::KS][C::TJ];  // one register set per k-step
   auto read = [&](const unsigned char* st, int ks, int buf) {
 #pragma unroll
     for (int i = 0; i < C::TI; ++i)
-      fa[buf][i] = *reinterpret_cast<const bf16x8*>(st + (a_row0 + 32 * i) * 128 + foff[ks]);
+      fa[buf][i] = *reinterpret_cast<const bf16x8*>(st + (a_row0 + C::MF * i) * 128 + foff[ks]);
 #pragma unroll
     for (int j = 0; j < C::TJ; ++j)
-      fb[buf][j] = *reinterpret_cast<const bf16x8*>(st + (b_row0 + 32 * j) * 128 + foff[ks]);
+      fb[buf][j] = *reinterpret_cast<const bf16x8*>(st + (b_row0 + C::MF * j) * 128 + foff[ks]);
   };
   // One K step in ring slot SLOT (a compile-time constant, so that every
   // fragment address is a loop-invariant base plus an immediate offset).
@@ -188,8 +197,8 @@ __device__ __forceinline__ void gemm_dma_body(const bf16* __restrict__ A, const 
     constexpr int slot = decltype(SLOT)::value, nslot = slot + 1 == NS ? 0 : slot + 1;
     const unsigned char* st = smem + slot * C::STAGE;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      if (ks < 3) {
+    for (int ks = 0; ks < C::KS; ++ks) {
+      if (ks + 1 < C::KS) {
         read(st, ks + 1, ks + 1);
       } else if (kt + 1 < KT) {
         sync_stage();
@@ -205,8 +214,12 @@ __device__ __forceinline__ void gemm_dma_body(const bf16* __restrict__ A, const 
 #pragma unroll
       for (int i = 0; i < C::TI; ++i)
 #pragma unroll
-        for (int j = 0; j < C::TJ; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < C::TJ; ++j) {
+          if constexpr (C::MF == 32)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
+          else
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
+        }
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -279,14 +292,14 @@ __device__ __forceinline__ void gemm_dma_body(const bf16* __restrict__ A, const 
         }
       }
       if (EH == 1 || wm == h) {  // four consecutive columns per 16-byte LDS store
-        float* srow = sC + (a_row0 - h * C::EROWS + r32) * C::CLD + wn * C::WN + 4 * g;
+        float* srow = sC + (a_row0 - h * C::EROWS + rf) * C::CLD + wn * C::WN + 4 * g;
 #pragma unroll
         for (int i = 0; i < C::TI; ++i)
 #pragma unroll
           for (int j = 0; j < C::TJ; ++j)
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-              *reinterpret_cast<float4*>(srow + i * 32 * C::CLD + j * 32 + 8 * q) =
+            for (int q = 0; q < C::NQ; ++q)
+              *reinterpret_cast<float4*>(srow + i * C::MF * C::CLD + j * C::MF + 8 * q) =
                   make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
       }
       __syncthreads();
@@ -415,6 +428,256 @@ __global__ __launch_bounds__(256, 2) void k_gemm_dma_mix(const bf16* __restrict_
       const int m0 = band + 192 * nb + (j / nt) * 128;
       if (m0 < M) gemm_dma_body<EPI, 128, 128, 2, 1>(A, W, bias, M, N, K, e, smem, m0, (j % nt) * 128);
     }
+  }
+}
+// ---------------------------------------------------------------------------
+// Tall tiles: 32 TI rows (TI 3 .. 8) x BN columns (192 or 256), one eight-wave
+// workgroup per CU.
+//  * Waves in 2x4, each 16 TI x BN/4 outputs; two stages of 64-deep K steps.
+//  * The chip is power-limited on these kernels (1.7-1.8 GHz in a stream of
+//    them), so a tile's worth is its bytes moved per FLOP: 256x256 copies 2/3 of
+//    the bytes of 192x128 from L2 to LDS and reads 4/5 of the fragment bytes.
+//    Rows of 128 bytes matter as well: half-line (64-byte) copies ran at half
+//    the L2 rate (1256 instead of 1115 cycles per 1024 of MFMA work).
+//  * Row i of a k-step (TJ MFMAs on fa[i]) is followed by the read of the next
+//    k-step's fa[i - 1], so one register set of A fragments serves both
+//    k-steps and only the W fragments are doubled; with both doubled the
+//    256-row tile spills.
+//  * The workgroup barrier stands two rows into the second k-step: by then the
+//    last fragments of the stage, read one row earlier, have arrived, and the
+//    copies of stage kt+2 have half a stage of MFMAs and more to land.
+//  * The epilogue needs no LDS: lanes l and l^16 exchange halves of two column
+//    blocks so that each stores 16 bytes, 64 contiguous bytes of a row per four
+//    lanes; the fp32 residual is read and written in 16-byte pieces the same way.
+// Against the two-per-CU tiles, streams of equal launches: M 9677, K 1024, N 3072
+// 65 -> 58 us and N 4096 88 -> 79; M 30925, N 1024, K 4096 (gated) 301 -> 241.
+// Every output starts at its bias and adds its products in ascending k, as in
+// the other tiles: same results.
+template <int EPI, int TI, int BN>
+__device__ __forceinline__ void gemm_tall_body(const bf16* __restrict__ A, const bf16* __restrict__ W,
+                                               const bf16* __restrict__ bias, int M, int K, const GemmEpi& e,
+                                               unsigned char* smem, int m0, int n0) {
+  constexpr int BM = 32 * TI, TJ = BN / 64, STAGE = (BM + BN) * 128;
+  constexpr int NC = (BM + BN) / 8, COPIES = (NC + 7) / 8;  // 8-row copies per stage, and per wave
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 2, wn = wave & 3, g = lane >> 4, r16 = lane & 15;
+  // copy c of this wave fills rows 8q .. 8q+7 of the stage (A rows, then W
+  // rows), q = 8c + wave; the last one only where q < NC
+  const bf16* src[COPIES];
+  uint32_t voff[COPIES];
+#pragma unroll
+  for (int c = 0; c < COPIES; ++c) {
+    const int q = 8 * c + wave, row = 8 * q + (lane >> 3);
+    const int ch = (lane & 7) ^ ((row >> 1) & 7);
+    if (8 * q < BM) {
+      src[c] = A;
+      voff[c] = 2u * (uint32_t)(min(m0 + row, M - 1) * K + ch * 8);
+    } else {
+      src[c] = W;
+      voff[c] = 2u * (uint32_t)((n0 + min(row - BM, BN - 1)) * K + ch * 8);
+    }
+  }
+  auto copy = [&](int kt, int slot, int c) {
+    if (NC % 8 == 0 || c + 1 < COPIES || wave < NC % 8)
+      lds_dma16_at(src[c] + kt * 64, voff[c], smem + slot * STAGE + (8 * c + wave) * 1024);
+  };
+  int foff[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) foff[ks] = r16 * 128 + (((4 * ks + g) ^ ((r16 >> 1) & 7)) << 4);
+  const int a0 = wm * 16 * TI, b0 = wn * 16 * TJ;
+  // transposed output blocks: lane l holds row a0 + 16 i + l%16 and columns
+  // b0 + 16 j + 4(l/16) .. + 3
+  f32x4 acc[TI][TJ];
+#pragma unroll
+  for (int j = 0; j < TJ; ++j) {
+    const bf16x4 b4 = *reinterpret_cast<const bf16x4*>(bias + n0 + b0 + j * 16 + 4 * g);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int i = 0; i < TI; ++i) acc[i][j][t] = (float)b4[t];
+  }
+  const int KT = K / 64;  // even (K is a multiple of 128)
+#pragma unroll
+  for (int st = 0; st < 2; ++st)
+#pragma unroll
+    for (int c = 0; c < COPIES; ++c) copy(st, st, c);
+  // stage 0 must land (a wave with one copy less per stage waits for one more)
+  __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(NC % 8 == 0 ? COPIES : COPIES - 1));
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  bf16x8 fa[2][TI], fb[2][TJ];
+  // fragment r of a k-step: the TJ of W first, then the TI of A
+  auto read = [&](int slot, int ks, int r) {
+    const unsigned char* st = smem + slot * STAGE + foff[ks];
+    if (r < TJ) fb[ks][r] = *reinterpret_cast<const bf16x8*>(st + (BM + b0 + 16 * r) * 128);
+    else fa[ks][r - TJ] = *reinterpret_cast<const bf16x8*>(st + (a0 + 16 * (r - TJ)) * 128);
+  };
+  auto row = [&](int ks, int i) {
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  constexpr int LAST = TJ + TI - 1;       // A fragment TI - 1, read at the start of its own k-step
+  constexpr int BR = TI >= 6 ? 2 : 1;     // rows of the second k-step before the barrier
+  constexpr int RR = TI - BR;             // and after it
+  auto step = [&](int kt, auto SLOT) {
+    constexpr int s = decltype(SLOT)::value;
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      if (i == 0) read(s, 0, LAST);
+      if (i < TJ) read(s, 1, i);
+      if (i >= 1) read(s, 1, TJ + i - 1);
+      if (TI < TJ && i + 1 == TI) read(s, 1, TJ - 1);
+      row(0, i);
+    }
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      if (i == 0) read(s, 1, LAST);
+      if (i == BR) {
+        // stage kt+1 has landed, and every wave has read all of stage kt
+        __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(0));
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+      }
+      if (i >= BR) {
+        // copies first; the last stages are refilled with the last one, which
+        // is not read again, so that the loop has no branch (one makes the
+        // 256-row tile spill)
+        constexpr int CR = RR > 1 ? RR - 1 : 1;
+#pragma unroll
+        for (int c = 0; c < COPIES; ++c)
+          if (c * CR / COPIES == i - BR) copy(min(kt + 2, KT - 1), s, c);
+        // the next stage's first k-step over the rows left; fa[r] not before row r + 1
+#pragma unroll
+        for (int r = 0; r < LAST; ++r) {
+          const int even = r * RR / LAST, after = r - TJ + 1 - BR;
+          if ((even > after ? even : after) == i - BR) read(s ^ 1, 0, r);
+        }
+      }
+      row(1, i);
+    }
+  };
+#pragma unroll
+  for (int r = 0; r < LAST; ++r) read(0, 0, r);
+  for (int kt = 0; kt < KT; kt += 2) {
+    step(kt, std::integral_constant<int, 0>{});
+    step(kt + 1, std::integral_constant<int, 1>{});
+  }
+  // the refills of the last stages must land while the workgroup holds its LDS
+  __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(0));
+  const bool qtile = EPI == EPI_BIAS && n0 < e.qcols;  // a column tile is all queries or none (launch rule)
+  if constexpr (EPI == EPI_GATED) {
+    int cr[TI];
+#pragma unroll
+    for (int i = 0; i < TI; ++i) cr[i] = e.crow[min(m0 + a0 + 16 * i + r16, M - 1)];
+    const int cr0 = __builtin_amdgcn_readfirstlane(cr[0]);
+    bool same = true;
+#pragma unroll
+    for (int i = 0; i < TI; ++i) same = same && cr[i] == cr0;
+    float* hb = static_cast<float*>(e.out) + n0 + b0 + 4 * g;
+    const float* gb = e.gate + n0 + b0 + 4 * g;
+    // residual loads run PD rows ahead of the stores (issued row by row, each
+    // would wait out a memory latency behind the previous row's stores)
+    constexpr int PD = TI < 4 ? TI : 4;
+    auto rows = [&](auto SAME) {
+      f32x4 g0[TJ], h[PD][TJ];
+      auto load = [&](int i) {
+        const float* hr = hb + (int64_t)min(m0 + a0 + 16 * i + r16, M - 1) * e.ldo;
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) h[i % PD][j] = *reinterpret_cast<const f32x4*>(hr + 16 * j);
+      };
+#pragma unroll
+      for (int i = 0; i < PD; ++i) load(i);
+      if constexpr (decltype(SAME)::value)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) g0[j] = *reinterpret_cast<const f32x4*>(gb + (int64_t)cr0 * e.ldg + 16 * j);
+#pragma unroll
+      for (int i = 0; i < TI; ++i) {
+        const int m = m0 + a0 + 16 * i + r16;
+        f32x4 gv[TJ];
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) {
+          if constexpr (decltype(SAME)::value) gv[j] = g0[j];
+          else gv[j] = *reinterpret_cast<const f32x4*>(gb + (int64_t)cr[i] * e.ldg + 16 * j);
+        }
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) {
+          f32x4 v;
+#pragma unroll
+          for (int t = 0; t < 4; ++t) v[t] = fmaf(1.0f + gv[j][t], acc[i][j][t], h[i % PD][j][t]);
+          if (m < M) *reinterpret_cast<f32x4*>(hb + (int64_t)m * e.ldo + 16 * j) = v;
+        }
+        if (i + PD < TI) load(i + PD);
+      }
+    };
+    // one conditioning row for the wave's rows (frames on one timestep): its gate is read once
+    if (__ballot(same) == ~0ull) rows(std::true_type{});
+    else rows(std::false_type{});
+  } else {
+    bf16* ob = static_cast<bf16*>(e.out) + n0 + b0;
+    const float qs = qtile ? e.qscale : 1.0f;
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      const int m = m0 + a0 + 16 * i + r16;
+      bf16* orow = ob + (int64_t)m * e.ldo;
+      uint2 p[TJ];
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) {
+        bf16x4 o;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          float v = acc[i][j][t];
+          if constexpr (EPI == EPI_GELU) v = gelu_tanh(v);
+          if constexpr (EPI == EPI_BIAS) v = qtile ? v * qs : v;
+          o[t] = (bf16)v;
+        }
+        p[j] = __builtin_bit_cast(uint2, o);
+      }
+      // columns 16 j .. 16 j + 31 in pairs of blocks: rows of 16 lanes 0, 2 end
+      // up with 8 columns of block j, rows 1, 3 with 8 of block j + 1
+#pragma unroll
+      for (int j = 0; j + 1 < TJ; j += 2) {
+        const auto x = __builtin_amdgcn_permlane16_swap(p[j].x, p[j + 1].x, false, false);
+        const auto y = __builtin_amdgcn_permlane16_swap(p[j].y, p[j + 1].y, false, false);
+        const uint4 v = make_uint4(x[0], y[0], x[1], y[1]);
+        if (m < M) *reinterpret_cast<uint4*>(orow + 16 * j + 16 * (g & 1) + 8 * (g >> 1)) = v;
+      }
+      if constexpr (TJ % 2 == 1)
+        if (m < M) *reinterpret_cast<uint2*>(orow + 16 * (TJ - 1) + 4 * g) = p[TJ - 1];
+    }
+  }
+}
+
+// n1 row tiles of 32 t1 rows, then n2 of 32 t2 rows, each with all N / BN
+// column tiles.  Each part's tiles are dealt to the XCDs in contiguous ranges
+// of panels four row tiles high, column by column inside a panel, so that the
+// tiles an XCD runs at a time share few rows of A and of W in its L2 (M 30925,
+// N 4096, K 1024: 268 us in plain order, 227 in panels).
+struct TallPlan {
+  int t1, n1, t2, n2;
+};
+template <int EPI, int BN>
+__global__ __launch_bounds__(512, 2) void k_gemm_tall(const bf16* __restrict__ A, const bf16* __restrict__ W,
+                                                      const bf16* __restrict__ bias, int M, int N, int K, GemmEpi e,
+                                                      TallPlan p) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * (256 + BN) * 128];
+  const int nt = N / BN, first = p.n1 * nt;
+  const bool two = (int)blockIdx.x >= first;
+  const int rt = two ? p.n2 : p.n1, ti = two ? p.t2 : p.t1;
+  const int tile = xcd_tile((int)blockIdx.x - (two ? first : 0), rt * nt);
+  const int panel = tile / (4 * nt), rem = tile - panel * 4 * nt, ph = min(4, rt - 4 * panel);
+  const int m0 = (two ? 32 * p.t1 * p.n1 : 0) + (4 * panel + rem % ph) * 32 * ti, n0 = (rem / ph) * BN;
+  switch (ti) {
+    case 3: gemm_tall_body<EPI, 3, BN>(A, W, bias, M, K, e, smem, m0, n0); break;
+    case 4: gemm_tall_body<EPI, 4, BN>(A, W, bias, M, K, e, smem, m0, n0); break;
+    case 5: gemm_tall_body<EPI, 5, BN>(A, W, bias, M, K, e, smem, m0, n0); break;
+    case 6: gemm_tall_body<EPI, 6, BN>(A, W, bias, M, K, e, smem, m0, n0); break;
+    case 7: gemm_tall_body<EPI, 7, BN>(A, W, bias, M, K, e, smem, m0, n0); break;
+    default: gemm_tall_body<EPI, 8, BN>(A, W, bias, M, K, e, smem, m0, n0); break;
   }
 }
 }  // namespace dma
@@ -622,6 +885,71 @@ double tile_rounds(int64_t tiles, int64_t slots, double w) {
   return w * ((double)full + (rem == 0 ? 0.0 : rem * 2 <= slots ? 0.5 : 1.0));
 }
 
+// Estimated times (us) of one round of tiles, for choosing between the tile
+// families: fitted on 64 block GEMMs of M 400 to 30925 at hidden sizes 512,
+// 1024 and 1152 (each in a stream of equal launches, so at power-limited
+// clocks); k is K in units of 1024, an h-row tile's cost grows with h.
+// Two 192x128 tiles per CU: 24 us at M 3226, N 3072, K 1024.
+double pair_round(int K, bool gated) {
+  const double k = K / 1024.0;
+  return 4.0 + 20.6 * k + (gated ? 6.0 : 0.0);
+}
+// One tall tile of h x bn per CU: 18.5, 26.9 and 29.8 us at 128, 224 and 256
+// rows of 256 columns, K 1024; gated 64 and 107 us at 128 and 256 rows, K 4096
+// (the residual's read and write is not hidden by another workgroup).
+double tall_round(int h, int bn, int K, bool gated) {
+  const double k = K / 1024.0, cols = h * bn / 256.0;
+  return (gated ? 4.0 : 1.4) + 5.2 * k + cols * ((gated ? 0.073 : 0.03) + 0.06 * k);
+}
+// The fastest plan of tall tiles by that estimate: equal row tiles, or whole
+// rounds of one height and one round of another for the rows left.
+struct TallChoice {
+  int bn = 0;
+  dma::TallPlan p{8, 0, 8, 0};
+  double us = 1e30;
+};
+TallChoice choose_tall(int epi, int M, int N, int K, int qcols, int cus) {
+  TallChoice best;
+  const bool gated = epi == EPI_GATED;
+  for (int bn : {256, 192}) {
+    if (N % bn != 0 || (epi == EPI_BIAS && qcols % bn != 0)) continue;
+    const int64_t nt = N / bn;
+    auto take = [&](const dma::TallPlan& p, double us) {
+      if (us < best.us) best = TallChoice{bn, p, us};
+    };
+    for (int t = 3; t <= 8; ++t) {
+      const int64_t n = (M + 32 * t - 1) / (32 * t);
+      take(dma::TallPlan{t, (int)n, t, 0}, (double)((n * nt + cus - 1) / cus) * tall_round(32 * t, bn, K, gated));
+    }
+    const int64_t per = cus / nt;  // row tiles of a round
+    if (per == 0) continue;
+    for (int t1 = 6; t1 <= 8; ++t1) {
+      const int64_t r = M / (32 * t1 * per), n1 = r * per, left = M - n1 * 32 * t1;
+      if (r == 0 || left == 0) continue;
+      const int64_t t2 = std::max<int64_t>(3, (left + 32 * per - 1) / (32 * per));
+      if (t2 > 8) continue;
+      take(dma::TallPlan{t1, (int)n1, (int)t2, (int)((left + 32 * t2 - 1) / (32 * t2))},
+           r * tall_round(32 * t1, bn, K, gated) + tall_round(32 * (int)t2, bn, K, gated));
+    }
+  }
+  return best;
+}
+
+void launch_tall(int epi, const TallChoice& c, const bf16* a, const bf16* w, const bf16* b, int M, int N, int K,
+                 const GemmEpi& e, hipStream_t s) {
+  const int grid = (c.p.n1 + c.p.n2) * (N / c.bn);
+  auto go = [&](auto E, auto BN) {
+    dma::k_gemm_tall<decltype(E)::value, decltype(BN)::value><<<grid, 512, 0, s>>>(a, w, b, M, N, K, e, c.p);
+  };
+  auto by_bn = [&](auto E) {
+    if (c.bn == 256) go(E, std::integral_constant<int, 256>{});
+    else go(E, std::integral_constant<int, 192>{});
+  };
+  if (epi == EPI_BIAS) by_bn(std::integral_constant<int, EPI_BIAS>{});
+  else if (epi == EPI_GELU) by_bn(std::integral_constant<int, EPI_GELU>{});
+  else by_bn(std::integral_constant<int, EPI_GATED>{});
+}
+
 // One eight-wave workgroup per BM-row tile with an NS-stage ring.
 template <int NS, int BM>
 void launch_deep(int epi, int tiles, const bf16* a, const bf16* w, const bf16* b, int M, int N, int K,
@@ -641,10 +969,12 @@ hipError_t launch_gemm(int epi, sphinx_dtype dt, const void* A, const void* W, c
     {
       const int64_t nt = N / 128, slots = 2 * (int64_t)cu_count();
       const int64_t t128 = nt * ((M + 127) / 128), t192 = nt * ((M + 191) / 192);
+      const int64_t cus = slots / 2, t256 = nt * ((M + 255) / 256), t64 = nt * ((M + 63) / 64);
       // few tiles: the smallest row tile (128, 192 or 256 rows) whose tiles
       // all fit on the CUs at once, one per CU with a deeper ring (128, 160
-      // or 144 KB of LDS; 64-row tiles 96 KB)
-      const int64_t cus = slots / 2, t256 = nt * ((M + 255) / 256), t64 = nt * ((M + 63) / 64);
+      // or 144 KB of LDS; 64-row tiles 96 KB).  Tall tiles give nothing that a
+      // step shows here (MLP1 at M 1613: 18.7 us against 19.1 alone, the step
+      // within its noise)
       if (t128 <= cus || t192 <= cus || t256 <= cus) {
         // 64-row tiles where 128-row ones would leave more than half the CUs idle
         if (t64 <= cus && 2 * t128 <= cus) launch_deep<4, 64>(epi, (int)t64, a, w, b, M, N, K, e, s);
@@ -661,6 +991,16 @@ hipError_t launch_gemm(int epi, sphinx_dtype dt, const void* A, const void* W, c
         nb = std::max(0, (need - 128 * per + 63) / 64);
         ns = per - nb;
         if (nb * 2 > per) nb = -1;  // some CU would hold two 192-row tiles
+      }
+      // tall tiles where they are estimated faster than two 192- or 128-row
+      // tiles per CU; the narrow mix below takes three quarters of a round
+      // (M 9677: out-projection 27 us against 30 on tall tiles, MLP2 73 against 75)
+      const TallChoice tall = choose_tall(epi, M, N, K, e.qcols, (int)cus);
+      const double pair = pair_round(K, epi == EPI_GATED) *
+                          (nb >= 0 ? 0.75 : std::min(tile_rounds(t192, slots, 1.0), tile_rounds(t128, slots, 1.0 / 1.41)));
+      if (tall.us < pair) {
+        launch_tall(epi, tall, a, w, b, M, N, K, e, s);
+        return hipGetLastError();
       }
       // wide N needing more than three rounds of 192-row tiles: the last round
       // all 128-row tiles (ns per column tile), 192-row tiles before it
