@@ -13,12 +13,12 @@
 //   iff any of its pixels is.
 // Every stencil reads its input map with replicated borders.
 //
-// Kernels (one pass over each input, Wm stored as 8 bytes per pixel and inv
+// Kernels (one pass over each input, Wm stored as a double per pixel and inv
 // as 1):
-//   k_front_var     per 64x16 tile: the stencil chain in LDS, Wm stored, tile
-//                   min/max of Wm;
+//   k_front_var     per tile of up to 240x16: the stencil chain in registers,
+//                   Wm stored, tile min/max of Wm;
 //   k_front_minmax  per frame: min/max over its tiles; clears the histogram;
-//   k_front_quant   per 64x16 tile: inv as bytes from the stored Wm, LDS
+//   k_front_quant   per 4096 pixels: inv as bytes from the stored Wm, LDS
 //                   histogram merged into the frame's histogram with integer
 //                   atomics;
 //   k_front_otsu    per frame: Otsu threshold from the 256-bin histogram;
@@ -28,218 +28,318 @@
 namespace sphinx {
 
 namespace {
-constexpr int kTX = 64, kTY = 16;  // output tile
-constexpr int kRV = 4, kRS = 2;    // 9x9 variance window, 5x5 smoothing
-constexpr int kHalo = 1 + kRV + kRS;
-// LDS regions (rows x cols), relative to the tile origin
-constexpr int kGY = kTY + 2 * kHalo, kGX = kTX + 2 * kHalo;              // luma: halo 7
-constexpr int kLY = kTY + 2 * (kHalo - 1), kLX = kTX + 2 * (kHalo - 1);  // Laplacian: halo 6
-constexpr int kSY = kLY, kSX = kTX + 2 * kRS;                            // row sums of L, L^2
-constexpr int kVY = kTY + 2 * kRS, kVX = kTX + 2 * kRS;                  // V: halo 2
 constexpr int kTPB = 256;
-
-// |L| <= 1020 and |sum of 9 L| <= 9180 fit 16 bits; the row sums of V reuse
-// the space of the luma .. row-sum regions, which are dead by then.
-struct FrontEarly {
-  int16_t gray[kGY * kGX];
-  int16_t lap[kLY * kLX];
-  int16_t s1[kSY * kSX];
-  int32_t s2[kSY * kSX];
-};
-struct FrontSmem {
-  union {
-    FrontEarly e;
-    int64_t r5[kVY * kTX];
-  };
-  int64_t v[kVY * kVX];
-  int64_t red[2 * kTPB / kWave];
-};
-static_assert(sizeof(int64_t) * kVY * kTX <= sizeof(FrontEarly), "row sums of V must fit the early regions");
+constexpr int kTY = 16;                      // output rows of a tile (image heights are multiples of 16)
+constexpr int kTXMax = 240;                  // output columns of a tile, at most: 64 lanes x 4 less the halo
+constexpr int kHaloX = 8;                    // 1 (Laplacian) + 4 (9-wide window) + 2 (5-wide box), to 4-column lanes
+constexpr int kWinL = 9, kWinV = 5;          // rows of the variance window and of the box
+constexpr int kQuantPix = 4096;              // pixels per k_front_quant workgroup
+constexpr int kHistCopies = 16;
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return min(max(v, lo), hi); }
 
-// Tile -> (request, frame, tile origin) for the packed frames of all requests.
-struct TileLoc {
-  int r, g, y0, x0, H, W;
-  int64_t pix0;  // first pixel of the frame
-};
+// Tiles across an image of W columns, and a tile's columns: the least number
+// of tiles, their widths even to within 4 columns.
+__host__ __device__ __forceinline__ int tiles_across(int W) { return (W + kTXMax - 1) / kTXMax; }
+__host__ __device__ __forceinline__ int tile_cols(int W) {
+  const int n = tiles_across(W);
+  return 4 * ((W / 4 + n - 1) / n);
+}
 
-__device__ __forceinline__ TileLoc locate_tile(const ReqTable& T, const FrontTiles& F, int tile) {
+// Wave shifts by one lane (DPP; they run at the rate of a move and take no LDS).
+// Lane 0 of from_left and lane 63 of from_right get 0; those are halo lanes.
+__device__ __forceinline__ int from_left(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xf, 0xf, true); }
+__device__ __forceinline__ int from_right(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xf, 0xf, true); }
+__device__ __forceinline__ double from_left(double v) {
+  return __hiloint2double(from_left(__double2hiint(v)), from_left(__double2loint(v)));
+}
+__device__ __forceinline__ double from_right(double v) {
+  return __hiloint2double(from_right(__double2hiint(v)), from_right(__double2loint(v)));
+}
+__device__ __forceinline__ double read_lane(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// Luma of the four pixels of 12 interleaved RGB bytes.
+struct Raw {
+  uint32_t d[3];
+};
+__device__ __forceinline__ void luma4(const Raw& q, int (&y)[4]) {
+  y[0] = (int)(__builtin_amdgcn_udot4(q.d[0], 0x001D964Du, 128u, false) >> 8);
+  y[1] = (int)(__builtin_amdgcn_udot4(q.d[0], 0x4D000000u,
+                                      __builtin_amdgcn_udot4(q.d[1], 0x00001D96u, 128u, false), false) >> 8);
+  y[2] = (int)(__builtin_amdgcn_udot4(q.d[1], 0x964D0000u,
+                                      __builtin_amdgcn_udot4(q.d[2], 0x0000001Du, 128u, false), false) >> 8);
+  y[3] = (int)(__builtin_amdgcn_udot4(q.d[2], 0x1D964D00u, 128u, false) >> 8);
+}
+
+// The stencil chain, one wave per tile of up to 240 x 16 pixels: a lane owns
+// four columns and streams down the rows.  Bound by VALU issue, so no stage
+// goes through LDS with a neighbour and none is done twice down a column:
+//  * vertical windows (9 rows of L and L^2, 5 of V) are running sums, whose
+//    leaving rows come from a ring in LDS that only the lane itself reads;
+//  * horizontal windows are a lane's own prefix and suffix sums plus those of
+//    its two neighbours (DPP wave shifts);
+//  * V and everything after it is whole numbers below 2^38 in doubles: exact,
+//    at one instruction per addition where 64-bit integers take two;
+//  * the next row's bytes are loaded a row ahead.
+// 16 rows a tile, because 14 frames of 576 x 1024 then give 2.5 waves per SIMD;
+// 14.5 KB of ring per wave lets 11 waves share a CU.
+// Borders: columns past the image take the edge column's luma (clamped loads),
+// vertical sums of L, L^2, and of V (one lane's value for all lanes outside);
+// rows past it repeat the edge row's L and V (the stream does not advance).
+// Stores Wm at the tile's pixels and the tile's min and max of Wm to
+// part[2 tile .. 2 tile + 1].
+// A 64 x 16 tile per workgroup with every stage in LDS took 100 us for
+// 14 frames of 576 x 1024; this takes 35 us.
+__global__ __launch_bounds__(kWave) void k_front_var(ReqTable T, FrontTiles F, const uint8_t* __restrict__ rgb,
+                                                     double* __restrict__ part, double* __restrict__ wm) {
+  typedef double f64x2 __attribute__((ext_vector_type(2)));
+  __shared__ int2 ring_l[kWinL][kWave];
+  __shared__ f64x2 ring_v[kWinV][2][kWave];
+  const int lane = threadIdx.x;
+  const int tile = blockIdx.x;
   int r = 0;
   while (r + 1 < T.R && F.tile_off[r + 1] <= tile) ++r;
-  TileLoc L;
-  L.r = r;
-  L.H = 8 * T.h[r];
-  L.W = 8 * T.w[r];
-  const int ntx = (L.W + kTX - 1) / kTX, nty = L.H / kTY;
+  const int H = 8 * T.h[r], W = 8 * T.w[r];
+  const int ntx = tiles_across(W), nty = H / kTY, cols = tile_cols(W);
   const int loc = tile - F.tile_off[r];
   const int f = loc / (ntx * nty), rem = loc - f * ntx * nty;
-  L.g = T.frame_off[r] + f;
-  L.y0 = (rem / ntx) * kTY;
-  L.x0 = (rem % ntx) * kTX;
-  const int64_t tpf = (int64_t)(T.h[r] >> 1) * (T.w[r] >> 1);
-  L.pix0 = 256 * (T.tok_off[r] + (int64_t)f * tpf);
-  return L;
-}
+  const int y0 = (rem / ntx) * kTY, x0 = (rem % ntx) * cols, x1 = min(x0 + cols, W);
+  const int64_t pix0 = 256 * (T.tok_off[r] + (int64_t)f * (T.h[r] >> 1) * (T.w[r] >> 1));  // the frame's first
+  const int xs = x0 - kHaloX, x = xs + 4 * lane;
+  const bool out_l = x < 0, out_r = x >= W;           // the lane's four columns lie left or right of the image
+  const bool edge_l = xs < 0, edge_r = xs + 4 * kWave > W;  // the tile has such lanes
+  const int last = (W - 4 - xs) >> 2;                 // the lane of the last image column (edge_r)
+  const uint8_t* img = rgb + 3 * (pix0 + clampi(x, 0, W - 4));
+  auto load = [&](int y) {
+    const uint32_t* p = reinterpret_cast<const uint32_t*>(img + 3 * (int64_t)clampi(y, 0, H - 1) * W);
+    return Raw{{p[0], p[1], p[2]}};
+  };
+  auto luma = [&](const Raw& q, int (&y)[4]) {
+    luma4(q, y);
+    if (edge_l || edge_r) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) y[e] = out_l ? y[0] : y[e];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) y[e] = out_r ? y[3] : y[e];
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < kWinL; ++i) ring_l[i][lane] = make_int2(0, 0);
+#pragma unroll
+  for (int i = 0; i < kWinV; ++i) ring_v[i][0][lane] = ring_v[i][1][lane] = f64x2{0.0, 0.0};
 
-// The stencil chain of one 64 x 16 tile in LDS: stores Wm at the tile's
-// in-image pixels and writes the tile's min and max of Wm to
-// part[2 tile .. 2 tile + 1].
-__global__ __launch_bounds__(kTPB) void k_front_var(ReqTable T, FrontTiles F, const uint8_t* __restrict__ rgb,
-                                                    int64_t* __restrict__ part, int64_t* __restrict__ wm) {
-  __shared__ FrontSmem sm;
-  const int tid = threadIdx.x;
-  const TileLoc L = locate_tile(T, F, blockIdx.x);
-  const int H = L.H, W = L.W, y0 = L.y0, x0 = L.x0;
-  const uint8_t* img = rgb + 3 * L.pix0;
-  // luma at clamped positions
-  for (int i = tid; i < kGY * kGX; i += kTPB) {
-    const int ry = i / kGX, rx = i - ry * kGX;
-    const int y = clampi(y0 - kHalo + ry, 0, H - 1), x = clampi(x0 - kHalo + rx, 0, W - 1);
-    const uint8_t* p = img + 3 * ((int64_t)y * W + x);
-    sm.e.gray[i] = (int16_t)((77 * (int)p[0] + 150 * (int)p[1] + 29 * (int)p[2] + 128) >> 8);
-  }
-  __syncthreads();
-  // Laplacian at the clamped position of every region pixel
-  for (int i = tid; i < kLY * kLX; i += kTPB) {
-    const int ry = i / kLX, rx = i - ry * kLX;
-    const int y = clampi(y0 - (kHalo - 1) + ry, 0, H - 1) - (y0 - kHalo);  // in luma-region coordinates
-    const int x = clampi(x0 - (kHalo - 1) + rx, 0, W - 1) - (x0 - kHalo);
-    const int16_t* g = sm.e.gray + y * kGX + x;
-    sm.e.lap[i] = (int16_t)(g[-kGX] + g[kGX] + g[-1] + g[1] - 4 * g[0]);
-  }
-  __syncthreads();
-  // horizontal 9-sums of L and L^2 around the clamped column
-  for (int i = tid; i < kSY * kSX; i += kTPB) {
-    const int ry = i / kSX, rx = i - ry * kSX;
-    const int x = clampi(x0 - kRS + rx, 0, W - 1) - (x0 - (kHalo - 1));  // in Laplacian-region columns
-    const int16_t* l = sm.e.lap + ry * kLX + x;
-    int a = 0, b = 0;
+  // rows c - 1, c, c + 1 of luma around the Laplacian row c, and row c + 2's bytes
+  const int v0 = clampi(y0 - 2, 0, H - 1);  // first row of V
+  int rl = v0 - 4;                          // next row of L (may lie above the image)
+  int c = clampi(rl, 0, H - 1);
+  int up[4], cu[4], dn[4];
+  luma(load(c - 1), up);
+  luma(load(c), cu);
+  luma(load(c + 1), dn);
+  Raw ahead = load(c + 2);
+  int s1[4] = {0, 0, 0, 0}, s2[4] = {0, 0, 0, 0};  // sums of L and L^2 over the last 9 rows of L, per column
+  int slot_l = 0;
+  auto push_l = [&]() {
+    if (clampi(rl, 0, H - 1) != c) {
+      ++c;
 #pragma unroll
-    for (int d = -kRV; d <= kRV; ++d) {
-      const int v = l[d];
-      a += v;
-      b += v * v;
+      for (int e = 0; e < 4; ++e) {
+        up[e] = cu[e];
+        cu[e] = dn[e];
+      }
+      luma(ahead, dn);
+      ahead = load(c + 2);
     }
-    sm.e.s1[i] = (int16_t)a;
-    sm.e.s2[i] = b;
-  }
-  __syncthreads();
-  // V = 81 sum(L^2) - (sum L)^2 over the 9x9 window of the clamped position
-  for (int i = tid; i < kVY * kVX; i += kTPB) {
-    const int ry = i / kVX, rx = i - ry * kVX;
-    const int y = clampi(y0 - kRS + ry, 0, H - 1) - (y0 - (kHalo - 1));  // in row-sum-region rows
-    int64_t a = 0, b = 0;
+    ++rl;
+    const int left = from_left(cu[3]), right = from_right(cu[0]);
+    int l[4];
 #pragma unroll
-    for (int d = -kRV; d <= kRV; ++d) {
-      a += sm.e.s1[(y + d) * kSX + rx];
-      b += sm.e.s2[(y + d) * kSX + rx];
+    for (int e = 0; e < 4; ++e)
+      l[e] = up[e] + dn[e] + (e == 0 ? left : cu[e - 1]) + (e == 3 ? right : cu[e + 1]) - 4 * cu[e];
+    const int2 old = ring_l[slot_l][lane];  // |L| <= 1020: two to a word
+    ring_l[slot_l][lane] = make_int2((l[0] & 0xffff) | (l[1] << 16), (l[2] & 0xffff) | (l[3] << 16));
+    slot_l = slot_l + 1 == kWinL ? 0 : slot_l + 1;
+    const int o[4] = {(int)(int16_t)old.x, old.x >> 16, (int)(int16_t)old.y, old.y >> 16};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      s1[e] += l[e] - o[e];
+      s2[e] += __mul24(l[e], l[e]) - __mul24(o[e], o[e]);
     }
-    sm.v[i] = 81 * b - a * a;
-  }
-  __syncthreads();
-  // horizontal 5-sums of V around the clamped column
-  for (int i = tid; i < kVY * kTX; i += kTPB) {
-    const int ry = i / kTX, rx = i - ry * kTX;
-    const int x = clampi(x0 + rx, 0, W - 1) - (x0 - kRS);
-    int64_t a = 0;
+  };
+  for (int i = 0; i < kWinL - 1; ++i) push_l();
+
+  double v[4] = {0.0, 0.0, 0.0, 0.0}, sv[4] = {0.0, 0.0, 0.0, 0.0};  // V, and its sum over the last 5 rows
+  int slot_v = 0, cv = -1;
+  double lo = __builtin_inf(), hi = -__builtin_inf();
+  for (int k = 0; k < kTY + kWinV - 1; ++k) {
+    const int cn = clampi(y0 - 2 + k, 0, H - 1);
+    if (cn != cv) {
+      cv = cn;
+      push_l();
+      int a[4], b[4];  // vertical sums, the edge column's in lanes outside the image
 #pragma unroll
-    for (int d = -kRS; d <= kRS; ++d) a += sm.v[ry * kVX + x + d];
-    sm.r5[i] = a;
-  }
-  __syncthreads();
-  // Wm at the tile's in-image pixels
-  int64_t lo = INT64_MAX, hi = INT64_MIN;
-  for (int i = tid; i < kTY * kTX; i += kTPB) {
-    const int ry = i / kTX, rx = i - ry * kTX;
-    const int y = y0 + ry, x = x0 + rx;
-    if (x >= W) continue;
-    const int yr = clampi(y, 0, H - 1) - (y0 - kRS);
-    int64_t w = 0;
+      for (int e = 0; e < 4; ++e) {
+        a[e] = s1[e];
+        b[e] = s2[e];
+      }
+      if (edge_l) {
+        const int a0 = __builtin_amdgcn_readlane(a[0], kHaloX / 4), b0 = __builtin_amdgcn_readlane(b[0], kHaloX / 4);
 #pragma unroll
-    for (int d = -kRS; d <= kRS; ++d) w += sm.r5[(yr + d) * kTX + rx];
-    wm[L.pix0 + (int64_t)y * W + x] = w;
-    lo = min(lo, w);
-    hi = max(hi, w);
+        for (int e = 0; e < 4; ++e) {
+          a[e] = out_l ? a0 : a[e];
+          b[e] = out_l ? b0 : b[e];
+        }
+      }
+      if (edge_r) {
+        const int a3 = __builtin_amdgcn_readlane(a[3], last), b3 = __builtin_amdgcn_readlane(b[3], last);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          a[e] = out_r ? a3 : a[e];
+          b[e] = out_r ? b3 : b[e];
+        }
+      }
+      // 9-wide window of column e: the left lane's last 4 - e columns, all four own, the right lane's first e + 1
+      int wa[4], wb[4];
+      auto window = [&](const int (&q)[4], int (&w)[4]) {
+        const int p2 = q[0] + q[1], p3 = p2 + q[2], u2 = q[2] + q[3], u3 = q[1] + u2, all = p2 + u2;
+        w[0] = from_left(all) + all + from_right(q[0]);
+        w[1] = from_left(u3) + all + from_right(p2);
+        w[2] = from_left(u2) + all + from_right(p3);
+        w[3] = from_left(q[3]) + all + from_right(all);
+      };
+      window(a, wa);
+      window(b, wb);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double da = (double)wa[e];
+        v[e] = fma(-da, da, 81.0 * (double)wb[e]);
+      }
+    }
+    const f64x2 o0 = ring_v[slot_v][0][lane], o1 = ring_v[slot_v][1][lane];
+    ring_v[slot_v][0][lane] = f64x2{v[0], v[1]};
+    ring_v[slot_v][1][lane] = f64x2{v[2], v[3]};
+    slot_v = slot_v + 1 == kWinV ? 0 : slot_v + 1;
+    sv[0] += v[0] - o0[0];
+    sv[1] += v[1] - o0[1];
+    sv[2] += v[2] - o1[0];
+    sv[3] += v[3] - o1[1];
+    if (k < kWinV - 1) continue;
+    double q[4] = {sv[0], sv[1], sv[2], sv[3]};
+    if (edge_l) {
+      const double q0 = read_lane(q[0], kHaloX / 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) q[e] = out_l ? q0 : q[e];
+    }
+    if (edge_r) {
+      const double q3 = read_lane(q[3], last);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) q[e] = out_r ? q3 : q[e];
+    }
+    // 5-wide box of column e, in the same manner
+    const double p2 = q[0] + q[1], u2 = q[2] + q[3], all = p2 + u2;
+    const double w0 = from_left(u2) + (p2 + q[2]), w1 = from_left(q[3]) + all;
+    const double w2 = all + from_right(q[0]), w3 = (q[1] + u2) + from_right(p2);
+    if (x >= x0 && x < x1) {
+      f64x2* o = reinterpret_cast<f64x2*>(wm + pix0 + (int64_t)(y0 + k - (kWinV - 1)) * W + x);
+      o[0] = f64x2{w0, w1};
+      o[1] = f64x2{w2, w3};
+      lo = fmin(fmin(lo, fmin(w0, w1)), fmin(w2, w3));
+      hi = fmax(fmax(hi, fmax(w0, w1)), fmax(w2, w3));
+    }
   }
   for (int m = 32; m >= 1; m >>= 1) {
-    lo = min(lo, (int64_t)__shfl_xor(lo, m, kWave));
-    hi = max(hi, (int64_t)__shfl_xor(hi, m, kWave));
+    lo = fmin(lo, __shfl_xor(lo, m, kWave));
+    hi = fmax(hi, __shfl_xor(hi, m, kWave));
   }
-  if (lane_id() == 0) {
-    sm.red[2 * (tid / kWave)] = lo;
-    sm.red[2 * (tid / kWave) + 1] = hi;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    for (int w = 1; w < kTPB / kWave; ++w) {
-      lo = min(lo, sm.red[2 * w]);
-      hi = max(hi, sm.red[2 * w + 1]);
-    }
-    part[2 * blockIdx.x] = lo;
-    part[2 * blockIdx.x + 1] = hi;
+  if (lane == 0) {
+    part[2 * tile] = lo;
+    part[2 * tile + 1] = hi;
   }
 }
 
-// Quantisation of one 64 x 16 tile's stored Wm with its frame's min/max
-// (lohi), four consecutive pixels of a row per thread: inv as bytes, and the
-// tile's histogram added to the frame's.
-__global__ __launch_bounds__(kTPB) void k_front_quant(ReqTable T, FrontTiles F, const int64_t* __restrict__ wm,
-                                                      const int64_t* __restrict__ lohi, uint8_t* __restrict__ inv,
+// Quantisation of 4096 consecutive pixels of a frame's stored Wm with the
+// frame's min/max (lohi), four at a time per thread: inv as bytes, and their
+// histogram added to the frame's.  Bound by the reads of Wm; the LDS atomics
+// would take longer than those where neighbouring pixels share a bin (a
+// blurred region is one value), so a bin has 16 counters in 16 banks, one for
+// every fourth lane of a wave.  One counter per bin and 64-bit integer
+// products took 36 us for 14 frames of 576 x 1024; this takes 16 us (4.6 TB/s).
+__global__ __launch_bounds__(kTPB) void k_front_quant(ReqTable T, FrontTiles Q, const double* __restrict__ wm,
+                                                      const double* __restrict__ lohi, uint8_t* __restrict__ inv,
                                                       uint32_t* __restrict__ hist) {
-  static_assert(kTX * kTY == 4 * kTPB, "four pixels per thread");
-  __shared__ uint32_t sh[256];
+  typedef double f64x2 __attribute__((ext_vector_type(2)));
+  constexpr int U = kQuantPix / (4 * kTPB);
+  __shared__ __attribute__((aligned(16))) uint32_t sh[256 * kHistCopies];
   const int tid = threadIdx.x;
-  const TileLoc L = locate_tile(T, F, blockIdx.x);
-  const int W = L.W;
-  sh[tid] = 0;
-  const int64_t flo = lohi[2 * L.g], fhi = lohi[2 * L.g + 1];
-  const double span = (double)(fhi - flo);
+  int r = 0;
+  while (r + 1 < T.R && Q.tile_off[r + 1] <= (int)blockIdx.x) ++r;
+  const int64_t pixels = (int64_t)64 * T.h[r] * T.w[r];  // of a frame
+  const int per = (int)((pixels + kQuantPix - 1) / kQuantPix);
+  const int loc = (int)blockIdx.x - Q.tile_off[r], f = loc / per, g = T.frame_off[r] + f;
+  const int64_t in_frame = (int64_t)(loc - f * per) * kQuantPix + 4 * tid;
+  const int64_t pix = 256 * T.tok_off[r] + f * pixels + in_frame;
+  f64x2 w[U][2];
+#pragma unroll
+  for (int i = 0; i < U; ++i)
+    if (in_frame + 4 * kTPB * i < pixels) {  // a frame is a multiple of 256 pixels: all four or none
+      const f64x2* p = reinterpret_cast<const f64x2*>(wm + pix + 4 * kTPB * i);
+      w[i][0] = p[0];
+      w[i][1] = p[1];
+    }
+#pragma unroll
+  for (int i = 0; i < kHistCopies; ++i) sh[tid + kTPB * i] = 0;
+  const double flo = lohi[2 * g], span = lohi[2 * g + 1] - flo;
+  const double scale = span > 0.0 ? 1.0 / span : 0.0;
   __syncthreads();
-  const int y = L.y0 + tid / (kTX / 4), x = L.x0 + 4 * (tid % (kTX / 4));
-  if (x < W) {  // W is a multiple of 8 pixels, so the four are all in the image or all past it
-    const int64_t pix = L.pix0 + (int64_t)y * W + x;
+  uint32_t* mine = sh + (tid & (kHistCopies - 1));
+#pragma unroll
+  for (int i = 0; i < U; ++i) {
+    if (in_frame + 4 * kTPB * i >= pixels) continue;
     uint32_t packed = 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int64_t w = wm[pix + e];
-      int q = 0;
-      if (fhi > flo) {
-        // floor(255 (w - lo) / (hi - lo)): a double quotient corrected to the exact floor
-        const int64_t num = 255 * (w - flo), den = fhi - flo;
-        int64_t qq = (int64_t)((double)num / span);
-        if (qq * den > num) --qq;
-        else if ((qq + 1) * den <= num) ++qq;
-        q = (int)qq;
-      }
-      const int iv = 255 - q;
+      // floor(255 (w - lo) / span): a rounded product is at most one off, and the remainder, which the fma
+      // gives exactly (all are whole numbers below 2^53), says which way
+      const double num = 255.0 * (w[i][e >> 1][e & 1] - flo);
+      const double q = floor(num * scale), rest = fma(-q, span, num);
+      int iv = 255 - (int)q;
+      if (span > 0.0) iv += rest < 0.0 ? 1 : (rest >= span ? -1 : 0);
       packed |= (uint32_t)iv << (8 * e);
-      atomicAdd(&sh[iv], 1u);
+      atomicAdd(mine + kHistCopies * iv, 1u);
     }
-    *reinterpret_cast<uint32_t*>(inv + pix) = packed;
+    *reinterpret_cast<uint32_t*>(inv + pix + 4 * kTPB * i) = packed;
   }
   __syncthreads();
-  if (sh[tid] != 0) atomicAdd(&hist[256 * L.g + tid], sh[tid]);
+  uint32_t sum = 0;
+#pragma unroll
+  for (int i = 0; i < kHistCopies / 4; ++i) {
+    const uint4 v = reinterpret_cast<const uint4*>(sh)[kHistCopies / 4 * tid + i];
+    sum += v.x + v.y + v.z + v.w;
+  }
+  if (sum != 0) atomicAdd(&hist[256 * g + tid], sum);
 }
 
 // Per frame: min and max of Wm over its tiles; clears the frame's histogram.
-__global__ __launch_bounds__(kTPB) void k_front_minmax(ReqTable T, FrontTiles F, const int64_t* __restrict__ part,
-                                                       int64_t* __restrict__ lohi, uint32_t* __restrict__ hist) {
-  __shared__ int64_t red[2 * kTPB / kWave];
+__global__ __launch_bounds__(kTPB) void k_front_minmax(ReqTable T, FrontTiles F, const double* __restrict__ part,
+                                                       double* __restrict__ lohi, uint32_t* __restrict__ hist) {
+  __shared__ double red[2 * kTPB / kWave];
   const int g = blockIdx.x, tid = threadIdx.x;
   int r = 0;
   while (r + 1 < T.R && T.frame_off[r + 1] <= g) ++r;
   const int W = 8 * T.w[r], H = 8 * T.h[r];
-  const int per = ((W + kTX - 1) / kTX) * (H / kTY);
+  const int per = tiles_across(W) * (H / kTY);
   const int t0 = F.tile_off[r] + (g - T.frame_off[r]) * per;
-  int64_t lo = INT64_MAX, hi = INT64_MIN;
+  double lo = __builtin_inf(), hi = -__builtin_inf();
   for (int i = tid; i < per; i += kTPB) {
-    lo = min(lo, part[2 * (t0 + i)]);
-    hi = max(hi, part[2 * (t0 + i) + 1]);
+    lo = fmin(lo, part[2 * (t0 + i)]);
+    hi = fmax(hi, part[2 * (t0 + i) + 1]);
   }
   for (int m = 32; m >= 1; m >>= 1) {
-    lo = min(lo, (int64_t)__shfl_xor(lo, m, kWave));
-    hi = max(hi, (int64_t)__shfl_xor(hi, m, kWave));
+    lo = fmin(lo, __shfl_xor(lo, m, kWave));
+    hi = fmax(hi, __shfl_xor(hi, m, kWave));
   }
   if (lane_id() == 0) {
     red[2 * (tid / kWave)] = lo;
@@ -249,11 +349,11 @@ __global__ __launch_bounds__(kTPB) void k_front_minmax(ReqTable T, FrontTiles F,
   __syncthreads();
   if (tid == 0) {
     for (int w = 1; w < kTPB / kWave; ++w) {
-      lo = min(lo, red[2 * w]);
-      hi = max(hi, red[2 * w + 1]);
+      lo = fmin(lo, red[2 * w]);
+      hi = fmax(hi, red[2 * w + 1]);
     }
-    lohi[2 * g] = min(lo, red[0]);
-    lohi[2 * g + 1] = max(hi, red[1]);
+    lohi[2 * g] = fmin(lo, red[0]);
+    lohi[2 * g + 1] = fmax(hi, red[1]);
   }
 }
 
@@ -389,9 +489,20 @@ int front_tiles(const ReqTable& T, FrontTiles* F) {
   for (int r = 0; r < T.R; ++r) {
     F->tile_off[r] = n;
     const int W = 8 * T.w[r], H = 8 * T.h[r];
-    n += T.frames[r] * ((W + kTX - 1) / kTX) * (H / kTY);
+    n += T.frames[r] * tiles_across(W) * (H / kTY);
   }
   F->tile_off[T.R] = n;
+  return n;
+}
+
+// Workgroups of k_front_quant, likewise.
+static int front_chunks(const ReqTable& T, FrontTiles* Q) {
+  int n = 0;
+  for (int r = 0; r < T.R; ++r) {
+    Q->tile_off[r] = n;
+    n += T.frames[r] * (int)(((int64_t)64 * T.h[r] * T.w[r] + kQuantPix - 1) / kQuantPix);
+  }
+  Q->tile_off[T.R] = n;
   return n;
 }
 
@@ -406,13 +517,13 @@ size_t front_ws_bytes(const ReqTable& T, int G) {
 
 hipError_t launch_front(const ReqTable& T, int G, const uint8_t* rgb, const float* opacity, float tau,
                         uint8_t* mask, float* u, int32_t* thr_out, void* ws, hipStream_t s) {
-  FrontTiles F;
-  const int tiles = front_tiles(T, &F);
+  FrontTiles F, Q;
+  const int tiles = front_tiles(T, &F), chunks = front_chunks(T, &Q);
   auto a256 = [](size_t b) { return (b + 255) & ~(size_t)255; };
   unsigned char* base = static_cast<unsigned char*>(ws);
-  int64_t* part = reinterpret_cast<int64_t*>(base);
+  double* part = reinterpret_cast<double*>(base);
   base += a256((size_t)tiles * 16);
-  int64_t* lohi = reinterpret_cast<int64_t*>(base);
+  double* lohi = reinterpret_cast<double*>(base);
   base += a256((size_t)G * 16);
   uint32_t* hist = reinterpret_cast<uint32_t*>(base);
   base += a256((size_t)G * 1024);
@@ -421,10 +532,10 @@ hipError_t launch_front(const ReqTable& T, int G, const uint8_t* rgb, const floa
   const int64_t pixels = 256 * T.tok_off[T.R];
   uint8_t* inv = base;
   base += a256((size_t)pixels);
-  int64_t* wm = reinterpret_cast<int64_t*>(base);
-  k_front_var<<<tiles, kTPB, 0, s>>>(T, F, rgb, part, wm);
+  double* wm = reinterpret_cast<double*>(base);
+  k_front_var<<<tiles, kWave, 0, s>>>(T, F, rgb, part, wm);
   k_front_minmax<<<G, kTPB, 0, s>>>(T, F, part, lohi, hist);
-  k_front_quant<<<tiles, kTPB, 0, s>>>(T, F, wm, lohi, inv, hist);
+  k_front_quant<<<chunks, kTPB, 0, s>>>(T, Q, wm, lohi, inv, hist);
   k_front_otsu<<<G, 256, 0, s>>>(hist, thr);
   const int64_t N = T.tok_off[T.R];
   k_front_pool<<<(unsigned)((N + 15) / 16), kTPB, 0, s>>>(T, opacity, tau, inv, thr, mask, u);

@@ -127,3 +127,17 @@ def test_pipeline_frontend_adaptive_refine():
     print(f"[pipeline] k = {list(ks)}, steps = {list(ns)}, masked = {int(ref_mask.sum())}/{wl.N}, "
           f"max_abs = {err:.3e}")
     assert err <= 2e-2
+
+
+@pytest.mark.parametrize("widths", [(2, 4, 28), (30, 32, 58), (60, 62, 88), (90, 92, 128)])
+def test_frontend_tile_edges(widths):
+    """Image widths around the 240-column tiles (one tile that ends with or
+    before its lanes, two and three, image edges in the halo of a neighbour)
+    and frames of one tile row and more, whose pixels end inside the 4096 of a
+    quantisation workgroup; all whole numbers, so bit for bit."""
+    reqs = [W.Request(2, h, w) for w, h in zip(widths, (2, 6, 4))]
+    rgb, opac = W.frontend_inputs(reqs, seed=31 + widths[0])
+    rng = np.random.default_rng(widths[0])
+    for a in rgb:  # one frame of noise: every column's value matters
+        a[1] = rng.integers(0, 256, a[1].shape, dtype=np.uint8)
+    check(reqs, rgb, [np.ones_like(o) for o in opac], tag=f"edges {widths}")
