@@ -17,9 +17,9 @@
 // as 1):
 //   k_front_var     per tile of up to 240x16: the stencil chain in registers,
 //                   Wm stored, tile min/max of Wm;
-//   k_front_minmax  per frame: min/max over its tiles; clears the histogram;
-//   k_front_quant   per 4096 pixels: inv as bytes from the stored Wm, LDS
-//                   histogram merged into the frame's histogram with integer
+//   k_front_minmax  per frame of many tiles: min/max over them;
+//   k_front_quant   per 4096 pixels: the frame's min/max from its tiles, inv
+//                   as bytes from the stored Wm, LDS histogram merged into the frame's histogram with integer
 //                   atomics;
 //   k_front_otsu    per frame: Otsu threshold from the 256-bin histogram;
 //   k_front_pool    per token: OR over its 16 x 16 pixels of both masks.
@@ -35,6 +35,7 @@ constexpr int kHaloX = 8;                    // 1 (Laplacian) + 4 (9-wide window
 constexpr int kWinL = 9, kWinV = 5;          // rows of the variance window and of the box
 constexpr int kQuantPix = 4096;              // pixels per k_front_quant workgroup
 constexpr int kHistCopies = 16;
+constexpr int kFewTiles = 512;               // tiles per frame up to which k_front_quant takes their min/max itself
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return min(max(v, lo), hi); }
 
@@ -90,11 +91,12 @@ __device__ __forceinline__ void luma4(const Raw& q, int (&y)[4]) {
 // vertical sums of L, L^2, and of V (one lane's value for all lanes outside);
 // rows past it repeat the edge row's L and V (the stream does not advance).
 // Stores Wm at the tile's pixels and the tile's min and max of Wm to
-// part[2 tile .. 2 tile + 1].
+// part[2 tile .. 2 tile + 1]; the first tile of a frame clears its histogram.
 // A 64 x 16 tile per workgroup with every stage in LDS took 100 us for
 // 14 frames of 576 x 1024; this takes 35 us.
 __global__ __launch_bounds__(kWave) void k_front_var(ReqTable T, FrontTiles F, const uint8_t* __restrict__ rgb,
-                                                     double* __restrict__ part, double* __restrict__ wm) {
+                                                     double* __restrict__ part, double* __restrict__ wm,
+                                                     uint32_t* __restrict__ hist) {
   typedef double f64x2 __attribute__((ext_vector_type(2)));
   __shared__ int2 ring_l[kWinL][kWave];
   __shared__ f64x2 ring_v[kWinV][2][kWave];
@@ -106,6 +108,7 @@ __global__ __launch_bounds__(kWave) void k_front_var(ReqTable T, FrontTiles F, c
   const int ntx = tiles_across(W), nty = H / kTY, cols = tile_cols(W);
   const int loc = tile - F.tile_off[r];
   const int f = loc / (ntx * nty), rem = loc - f * ntx * nty;
+  if (rem == 0) reinterpret_cast<uint4*>(hist + 256 * (T.frame_off[r] + f))[lane] = make_uint4(0, 0, 0, 0);
   const int y0 = (rem / ntx) * kTY, x0 = (rem % ntx) * cols, x1 = min(x0 + cols, W);
   const int64_t pix0 = 256 * (T.tok_off[r] + (int64_t)f * (T.h[r] >> 1) * (T.w[r] >> 1));  // the frame's first
   const int xs = x0 - kHaloX, x = xs + 4 * lane;
@@ -260,19 +263,74 @@ __global__ __launch_bounds__(kWave) void k_front_var(ReqTable T, FrontTiles F, c
   }
 }
 
+// Min and max of `n` (min, max) pairs, in every thread of a 256-thread workgroup.
+__device__ __forceinline__ void block_minmax(const double* __restrict__ part, int n, double (&red)[2 * kTPB / kWave],
+                                             double& lo, double& hi) {
+  const int tid = threadIdx.x;
+  lo = __builtin_inf();
+  hi = -__builtin_inf();
+  for (int i = tid; i < n; i += kTPB) {
+    lo = fmin(lo, part[2 * i]);
+    hi = fmax(hi, part[2 * i + 1]);
+  }
+  for (int m = 32; m >= 1; m >>= 1) {
+    lo = fmin(lo, __shfl_xor(lo, m, kWave));
+    hi = fmax(hi, __shfl_xor(hi, m, kWave));
+  }
+  if (lane_id() == 0) {
+    red[2 * (tid / kWave)] = lo;
+    red[2 * (tid / kWave) + 1] = hi;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kTPB / kWave; ++w) {
+    lo = fmin(lo, red[2 * w]);
+    hi = fmax(hi, red[2 * w + 1]);
+  }
+}
+
+// Tiles of one frame of request r.
+__device__ __forceinline__ int frame_tiles(const ReqTable& T, int r) {
+  return tiles_across(8 * T.w[r]) * (8 * T.h[r] / kTY);
+}
+
+// Per frame of more than kFewTiles tiles: min and max of Wm over them.
+__global__ __launch_bounds__(kTPB) void k_front_minmax(ReqTable T, FrontTiles F, const double* __restrict__ part,
+                                                       double* __restrict__ lohi) {
+  __shared__ double red[2 * kTPB / kWave];
+  const int g = blockIdx.x;
+  int r = 0;
+  while (r + 1 < T.R && T.frame_off[r + 1] <= g) ++r;
+  const int per = frame_tiles(T, r);
+  if (per <= kFewTiles) return;
+  double lo, hi;
+  block_minmax(part + 2 * (int64_t)(F.tile_off[r] + (g - T.frame_off[r]) * per), per, red, lo, hi);
+  if (threadIdx.x == 0) {
+    lohi[2 * g] = lo;
+    lohi[2 * g + 1] = hi;
+  }
+}
+
 // Quantisation of 4096 consecutive pixels of a frame's stored Wm with the
-// frame's min/max (lohi), four at a time per thread: inv as bytes, and their
+// frame's min/max, four at a time per thread: inv as bytes, and their
 // histogram added to the frame's.  Bound by the reads of Wm; the LDS atomics
 // would take longer than those where neighbouring pixels share a bin (a
 // blurred region is one value), so a bin has 16 counters in 16 banks, one for
 // every fourth lane of a wave.  One counter per bin and 64-bit integer
-// products took 36 us for 14 frames of 576 x 1024; this takes 16 us (4.6 TB/s).
-__global__ __launch_bounds__(kTPB) void k_front_quant(ReqTable T, FrontTiles Q, const double* __restrict__ wm,
+// products took 36 us for 14 frames of 576 x 1024; this takes 17 us (4.3 TB/s).
+// The min/max of a frame of up to kFewTiles tiles is taken here, from their 16
+// bytes each while the pixels' loads are in flight (at 512 tiles 8 KB from L2
+// beside the 32 KB of Wm): 1 us, where a launch of its own took 4.4 us at the
+// 180 tiles of those frames (whole call 73.1 -> 71.2 us).  Larger frames, where
+// the repeated reads would grow past the pixels, keep the launch (lohi).
+__global__ __launch_bounds__(kTPB) void k_front_quant(ReqTable T, FrontTiles F, FrontTiles Q,
+                                                      const double* __restrict__ wm, const double* __restrict__ part,
                                                       const double* __restrict__ lohi, uint8_t* __restrict__ inv,
                                                       uint32_t* __restrict__ hist) {
   typedef double f64x2 __attribute__((ext_vector_type(2)));
   constexpr int U = kQuantPix / (4 * kTPB);
   __shared__ __attribute__((aligned(16))) uint32_t sh[256 * kHistCopies];
+  __shared__ double red[2 * kTPB / kWave];
   const int tid = threadIdx.x;
   int r = 0;
   while (r + 1 < T.R && Q.tile_off[r + 1] <= (int)blockIdx.x) ++r;
@@ -291,7 +349,15 @@ __global__ __launch_bounds__(kTPB) void k_front_quant(ReqTable T, FrontTiles Q, 
     }
 #pragma unroll
   for (int i = 0; i < kHistCopies; ++i) sh[tid + kTPB * i] = 0;
-  const double flo = lohi[2 * g], span = lohi[2 * g + 1] - flo;
+  const int tiles = frame_tiles(T, r);
+  double flo, fhi;
+  if (tiles <= kFewTiles) {
+    block_minmax(part + 2 * (int64_t)(F.tile_off[r] + f * tiles), tiles, red, flo, fhi);
+  } else {
+    flo = lohi[2 * g];
+    fhi = lohi[2 * g + 1];
+  }
+  const double span = fhi - flo;
   const double scale = span > 0.0 ? 1.0 / span : 0.0;
   __syncthreads();
   uint32_t* mine = sh + (tid & (kHistCopies - 1));
@@ -320,41 +386,6 @@ __global__ __launch_bounds__(kTPB) void k_front_quant(ReqTable T, FrontTiles Q, 
     sum += v.x + v.y + v.z + v.w;
   }
   if (sum != 0) atomicAdd(&hist[256 * g + tid], sum);
-}
-
-// Per frame: min and max of Wm over its tiles; clears the frame's histogram.
-__global__ __launch_bounds__(kTPB) void k_front_minmax(ReqTable T, FrontTiles F, const double* __restrict__ part,
-                                                       double* __restrict__ lohi, uint32_t* __restrict__ hist) {
-  __shared__ double red[2 * kTPB / kWave];
-  const int g = blockIdx.x, tid = threadIdx.x;
-  int r = 0;
-  while (r + 1 < T.R && T.frame_off[r + 1] <= g) ++r;
-  const int W = 8 * T.w[r], H = 8 * T.h[r];
-  const int per = tiles_across(W) * (H / kTY);
-  const int t0 = F.tile_off[r] + (g - T.frame_off[r]) * per;
-  double lo = __builtin_inf(), hi = -__builtin_inf();
-  for (int i = tid; i < per; i += kTPB) {
-    lo = fmin(lo, part[2 * (t0 + i)]);
-    hi = fmax(hi, part[2 * (t0 + i) + 1]);
-  }
-  for (int m = 32; m >= 1; m >>= 1) {
-    lo = fmin(lo, __shfl_xor(lo, m, kWave));
-    hi = fmax(hi, __shfl_xor(hi, m, kWave));
-  }
-  if (lane_id() == 0) {
-    red[2 * (tid / kWave)] = lo;
-    red[2 * (tid / kWave) + 1] = hi;
-  }
-  for (int i = tid; i < 256; i += kTPB) hist[256 * g + i] = 0;
-  __syncthreads();
-  if (tid == 0) {
-    for (int w = 1; w < kTPB / kWave; ++w) {
-      lo = fmin(lo, red[2 * w]);
-      hi = fmax(hi, red[2 * w + 1]);
-    }
-    lohi[2 * g] = fmin(lo, red[0]);
-    lohi[2 * g + 1] = fmax(hi, red[1]);
-  }
 }
 
 // 192-bit value of a (128-bit) * b (64-bit), as three 64-bit limbs.
@@ -533,9 +564,11 @@ hipError_t launch_front(const ReqTable& T, int G, const uint8_t* rgb, const floa
   uint8_t* inv = base;
   base += a256((size_t)pixels);
   double* wm = reinterpret_cast<double*>(base);
-  k_front_var<<<tiles, kWave, 0, s>>>(T, F, rgb, part, wm);
-  k_front_minmax<<<G, kTPB, 0, s>>>(T, F, part, lohi, hist);
-  k_front_quant<<<chunks, kTPB, 0, s>>>(T, Q, wm, lohi, inv, hist);
+  k_front_var<<<tiles, kWave, 0, s>>>(T, F, rgb, part, wm, hist);
+  bool large = false;
+  for (int r = 0; r < T.R; ++r) large |= tiles_across(8 * T.w[r]) * (8 * T.h[r] / kTY) > kFewTiles;
+  if (large) k_front_minmax<<<G, kTPB, 0, s>>>(T, F, part, lohi);
+  k_front_quant<<<chunks, kTPB, 0, s>>>(T, F, Q, wm, part, lohi, inv, hist);
   k_front_otsu<<<G, 256, 0, s>>>(hist, thr);
   const int64_t N = T.tok_off[T.R];
   k_front_pool<<<(unsigned)((N + 15) / 16), kTPB, 0, s>>>(T, opacity, tau, inv, thr, mask, u);

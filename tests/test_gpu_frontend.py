@@ -141,3 +141,12 @@ def test_frontend_tile_edges(widths):
     for a in rgb:  # one frame of noise: every column's value matters
         a[1] = rng.integers(0, 256, a[1].shape, dtype=np.uint8)
     check(reqs, rgb, [np.ones_like(o) for o in opac], tag=f"edges {widths}")
+
+
+@pytest.mark.parametrize("h", [1024, 1026])
+def test_frontend_many_tiles(h):
+    """512 tiles per frame (their min/max taken by the quantisation) and 513
+    (taken by a launch of its own), the latter beside a small request."""
+    reqs = [W.Request(1, h, 2)] + ([W.Request(2, 6, 10)] if h > 1024 else [])
+    rgb, opac = W.frontend_inputs(reqs, seed=41)
+    check(reqs, rgb, [np.ones_like(o) for o in opac], tag=f"tiles {h // 2}")
