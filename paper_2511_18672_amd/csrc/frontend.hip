@@ -35,6 +35,7 @@ constexpr int kHaloX = 8;                    // 1 (Laplacian) + 4 (9-wide window
 constexpr int kWinL = 9, kWinV = 5;          // rows of the variance window and of the box
 constexpr int kQuantPix = 4096;              // pixels per k_front_quant workgroup
 constexpr int kHistCopies = 16;
+constexpr int kSplitTiles = 512;             // tiles up to which four waves share one
 constexpr int kFewTiles = 512;               // tiles per frame up to which k_front_quant takes their min/max itself
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return min(max(v, lo), hi); }
@@ -92,15 +93,25 @@ __device__ __forceinline__ void luma4(const Raw& q, int (&y)[4]) {
 // rows past it repeat the edge row's L and V (the stream does not advance).
 // Stores Wm at the tile's pixels and the tile's min and max of Wm to
 // part[2 tile .. 2 tile + 1]; the first tile of a frame clears its histogram.
+// NW waves share a tile's rows: one wave walks 28 rows in series to give 16, so
+// where the tiles would leave most of the 1024 SIMDs idle (up to 512 of them)
+// four waves walk 16 rows for 4 each, for 1.7 times the work.  A whole call on
+// small requests (a few hundred tokens on): 32 us with one wave, 24 with four (25 with
+// the tiles in LDS described below).
 // A 64 x 16 tile per workgroup with every stage in LDS took 100 us for
 // 14 frames of 576 x 1024; this takes 35 us.
-__global__ __launch_bounds__(kWave) void k_front_var(ReqTable T, FrontTiles F, const uint8_t* __restrict__ rgb,
+template <int NW>
+__global__ __launch_bounds__(NW * kWave) void k_front_var(ReqTable T, FrontTiles F, const uint8_t* __restrict__ rgb,
                                                      double* __restrict__ part, double* __restrict__ wm,
                                                      uint32_t* __restrict__ hist) {
   typedef double f64x2 __attribute__((ext_vector_type(2)));
-  __shared__ int2 ring_l[kWinL][kWave];
-  __shared__ f64x2 ring_v[kWinV][2][kWave];
-  const int lane = threadIdx.x;
+  constexpr int kRows = kTY / NW;
+  __shared__ int2 rings_l[NW][kWinL][kWave];
+  __shared__ f64x2 rings_v[NW][kWinV][2][kWave];
+  __shared__ double red[2 * NW];
+  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  auto& ring_l = rings_l[wave];
+  auto& ring_v = rings_v[wave];
   const int tile = blockIdx.x;
   int r = 0;
   while (r + 1 < T.R && F.tile_off[r + 1] <= tile) ++r;
@@ -108,8 +119,8 @@ __global__ __launch_bounds__(kWave) void k_front_var(ReqTable T, FrontTiles F, c
   const int ntx = tiles_across(W), nty = H / kTY, cols = tile_cols(W);
   const int loc = tile - F.tile_off[r];
   const int f = loc / (ntx * nty), rem = loc - f * ntx * nty;
-  if (rem == 0) reinterpret_cast<uint4*>(hist + 256 * (T.frame_off[r] + f))[lane] = make_uint4(0, 0, 0, 0);
-  const int y0 = (rem / ntx) * kTY, x0 = (rem % ntx) * cols, x1 = min(x0 + cols, W);
+  if (rem == 0 && wave == 0) reinterpret_cast<uint4*>(hist + 256 * (T.frame_off[r] + f))[lane] = make_uint4(0, 0, 0, 0);
+  const int y0 = (rem / ntx) * kTY + wave * kRows, x0 = (rem % ntx) * cols, x1 = min(x0 + cols, W);
   const int64_t pix0 = 256 * (T.tok_off[r] + (int64_t)f * (T.h[r] >> 1) * (T.w[r] >> 1));  // the frame's first
   const int xs = x0 - kHaloX, x = xs + 4 * lane;
   const bool out_l = x < 0, out_r = x >= W;           // the lane's four columns lie left or right of the image
@@ -177,7 +188,7 @@ __global__ __launch_bounds__(kWave) void k_front_var(ReqTable T, FrontTiles F, c
   double v[4] = {0.0, 0.0, 0.0, 0.0}, sv[4] = {0.0, 0.0, 0.0, 0.0};  // V, and its sum over the last 5 rows
   int slot_v = 0, cv = -1;
   double lo = __builtin_inf(), hi = -__builtin_inf();
-  for (int k = 0; k < kTY + kWinV - 1; ++k) {
+  for (int k = 0; k < kRows + kWinV - 1; ++k) {
     const int cn = clampi(y0 - 2 + k, 0, H - 1);
     if (cn != cv) {
       cv = cn;
@@ -257,7 +268,19 @@ __global__ __launch_bounds__(kWave) void k_front_var(ReqTable T, FrontTiles F, c
     lo = fmin(lo, __shfl_xor(lo, m, kWave));
     hi = fmax(hi, __shfl_xor(hi, m, kWave));
   }
-  if (lane == 0) {
+  if (NW > 1) {
+    if (lane == 0) {
+      red[2 * wave] = lo;
+      red[2 * wave + 1] = hi;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      lo = fmin(lo, red[2 * i]);
+      hi = fmax(hi, red[2 * i + 1]);
+    }
+  }
+  if (threadIdx.x == 0) {
     part[2 * tile] = lo;
     part[2 * tile + 1] = hi;
   }
@@ -564,7 +587,10 @@ hipError_t launch_front(const ReqTable& T, int G, const uint8_t* rgb, const floa
   uint8_t* inv = base;
   base += a256((size_t)pixels);
   double* wm = reinterpret_cast<double*>(base);
-  k_front_var<<<tiles, kWave, 0, s>>>(T, F, rgb, part, wm, hist);
+  if (tiles <= kSplitTiles)
+    k_front_var<4><<<tiles, 4 * kWave, 0, s>>>(T, F, rgb, part, wm, hist);
+  else
+    k_front_var<1><<<tiles, kWave, 0, s>>>(T, F, rgb, part, wm, hist);
   bool large = false;
   for (int r = 0; r < T.R; ++r) large |= tiles_across(8 * T.w[r]) * (8 * T.h[r] / kTY) > kFewTiles;
   if (large) k_front_minmax<<<G, kTPB, 0, s>>>(T, F, part, lohi);
