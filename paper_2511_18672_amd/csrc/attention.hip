@@ -856,12 +856,14 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(AttnIO io, int D, int d, Se
 #pragma unroll
     for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sc[r]);
     mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
-    const float mn = fmaxf(m, mx), corr = exp2f(m - mn);
+    // while every score of this wave is -inf (a product that overflowed) the base
+    // is 0: such keys weigh 0 and the other waves' keys decide
+    const float mn = fmaxf(m, mx), base = mn == -INFINITY ? 0.0f : mn, corr = exp2f(m - base);
     m = mn;
     float ps = 0.0f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      sc[r] = exp2f(sc[r] - mn);
+      sc[r] = exp2f(sc[r] - base);
       ps += sc[r];
     }
     l = fmaf(l, corr, ps);  // this lane's half of the keys
@@ -885,7 +887,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(AttnIO io, int D, int d, Se
   const int c = tid % DP;
   if (c >= d) return;
   for (int q = tid / DP; q < 32 && q0 + q < Lq; q += 256 / DP) {
-    // wave 0 has a tile, so mm is a real maximum; a wave without one weighs 0
+    // a wave without a tile, or with scores of -inf only, has m = -inf and weighs
+    // 0 (with no other score in the segment there is no softmax: NaN)
     const float mm = fmaxf(fmaxf(sM[0][q], sM[1][q]), fmaxf(sM[2][q], sM[3][q]));
     float num = 0.0f, den = 0.0f;
 #pragma unroll

@@ -44,3 +44,20 @@ def test_fp32_gemm_edges(D, heads, mlp, n):
     wl = W.custom(f"fp32_{D}_{n}", model, [W.Request(2, 16, 16)], [n / 128], [0.5], [2])
     R = check_end_to_end(wl)
     assert R.n_sel == n
+
+
+@pytest.mark.parametrize("hd", [16, 64])
+@pytest.mark.parametrize("tiles", [(0,), (1,), (1, 5, 9), (0, 4, 8, 1, 5, 9, 2, 6)])
+def test_fp32_attention_keys_of_no_weight(hd, tiles):
+    """Keys whose scores overflow to -inf (weight 0) fill whole 32-key tiles: the
+    first tile of a wave, every tile of one wave, all tiles of three waves.  The
+    other keys' softmax is what remains, so the bound is that of the edges above."""
+    rng = np.random.default_rng(len(tiles))
+    heads, n = 2, 300
+    D = heads * hd
+    q, k, v = rand(rng, n, D, 2.0 / np.sqrt(hd)), rand(rng, n, D), rand(rng, n, D)
+    for t in tiles:
+        k[32 * t:32 * t + 32, ::hd] = 3e38
+    q[:, ::hd] = -2.0
+    cu = np.array([0, n], np.int32)
+    check(q, k, v, heads, hd, cu, cu, dtype="f32", tag=f"fp32 no weight hd{hd} tiles {tiles}")
