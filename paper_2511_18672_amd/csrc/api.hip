@@ -744,9 +744,9 @@ sphinx_status refine_impl(const sphinx_model_desc* m, const sphinx_request* reqs
     {
       Bracket br(SPHINX_K_ATTENTION, s);
       if (!factorised)
-        SPHINX_TRY(launch_attention(dt, io, D, m->heads, m->head_dim, n, S, s));
+        SPHINX_TRY(launch_attention(dt, io, D, m->heads, m->head_dim, S, s));
       else if (l % 2 == 0)  // spatial: within the frame
-        SPHINX_TRY(launch_attention(dt, io, D, m->heads, m->head_dim, n, Sf, s));
+        SPHINX_TRY(launch_attention(dt, io, D, m->heads, m->head_dim, Sf, s));
       else  // temporal: across the request's frames at the same position
         SPHINX_TRY(launch_attn_temporal(dt, T, io, D, m->heads, m->head_dim, I32(W.pos), cached, s));
     }
@@ -833,7 +833,7 @@ sphinx_status sphinx_varlen_attention(sphinx_dtype dtype, int32_t heads, int32_t
   const AttnIO io{q, k, v, o, ldq, ldkv};
   hipStream_t s = (hipStream_t)stream;
   Bracket br(SPHINX_K_ATTENTION, s);
-  return hip_status(launch_attention(dtype, io, (int)D, heads, head_dim, (int)nq, S, s));
+  return hip_status(launch_attention(dtype, io, (int)D, heads, head_dim, S, s));
 }
 
 sphinx_status sphinx_scatter_blend(const sphinx_request* reqs, int32_t R, const float* x_sel, const int32_t* idx,

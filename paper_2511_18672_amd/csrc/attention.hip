@@ -782,7 +782,7 @@ __global__ __launch_bounds__(256, 3) void k_attn_bf16_dma72(AttnIO io, int D, in
 // DP: head_dim rounded up to 16, 32 or 64; VEC: head_dim a multiple of 4 (then
 // every row is 16-byte aligned), else element loads.
 template <int DP, bool VEC>
-__global__ __launch_bounds__(256, 2) void k_attn_f32(AttnIO io, int D, int d, SegTable S) {
+__global__ __launch_bounds__(256, 2) void k_attn_f32(AttnIO io, int D, int d, int first, int total, SegTable S) {
   constexpr int NJ = DP / 8, NB = (DP + 31) / 32;
   __shared__ float sO[4][NB * 32][33];
   __shared__ float sM[4][32], sL[4][32];
@@ -790,7 +790,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(AttnIO io, int D, int d, Se
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, r32 = lane & 31;
   const int tiles = S.tile_prefix[S.nseg] * (AQ / 32);
-  const int lid = xcd_tile((int)blockIdx.x, (int)gridDim.x);  // whole heads per XCD
+  const int lid = xcd_tile(first + (int)blockIdx.x, total);  // whole heads per XCD
   const int head = lid / tiles, sub = lid - head * tiles, tile = sub / (AQ / 32);
   int s = 0;
   while (s + 1 < S.nseg && S.tile_prefix[s + 1] <= tile) ++s;
@@ -902,8 +902,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(AttnIO io, int D, int d, Se
 }
 }  // namespace
 
-hipError_t launch_attention(sphinx_dtype dt, const AttnIO& io, int D, int heads, int head_dim, int n,
-                            const SegTable& S, hipStream_t s) {
+hipError_t launch_attention(sphinx_dtype dt, const AttnIO& io, int D, int heads, int head_dim, const SegTable& S,
+                            hipStream_t s) {
   if (dt == SPHINX_BF16) {
     const int grid = S.tile_prefix[S.nseg] * heads;
     if (head_dim == 64)
@@ -911,9 +911,13 @@ hipError_t launch_attention(sphinx_dtype dt, const AttnIO& io, int D, int heads,
     else
       k_attn_bf16_dma72<<<grid, 256, 0, s>>>(io, D, heads, S);
   } else {
-    const int grid = S.tile_prefix[S.nseg] * (AQ / 32) * heads;
+    // a launch holds 2^32 threads at most, which the narrowest heads exceed (131073
+    // queries of 4096 heads of one dim): 2^23 workgroups at a time, a multiple of the XCDs
+    const int total = S.tile_prefix[S.nseg] * (AQ / 32) * heads, most = 1 << 23;
     auto go = [&](auto dp, auto vec) {
-      k_attn_f32<decltype(dp)::value, decltype(vec)::value><<<grid, 256, 0, s>>>(io, D, head_dim, S);
+      for (int first = 0; first < total; first += most)
+        k_attn_f32<decltype(dp)::value, decltype(vec)::value>
+            <<<std::min(most, total - first), 256, 0, s>>>(io, D, head_dim, first, total, S);
     };
     auto by_dim = [&](auto vec) {
       if (head_dim <= 16) go(std::integral_constant<int, 16>{}, vec);

@@ -110,8 +110,8 @@ hipError_t launch_gemm(int epi, sphinx_dtype dt, const void* A, const void* W, c
 hipError_t launch_peak_mfma(int iters, bool random, float* out, int blocks, hipStream_t s);
 
 // attention.hip
-hipError_t launch_attention(sphinx_dtype dt, const AttnIO& io, int D, int heads, int head_dim, int n,
-                            const SegTable& S, hipStream_t s);
+hipError_t launch_attention(sphinx_dtype dt, const AttnIO& io, int D, int heads, int head_dim, const SegTable& S,
+                            hipStream_t s);
 // Temporal attention of a factorised denoiser: pos[t] = forwarded row of token t
 // or -1; keys are the forwarded tokens of the column (or all of its frames from
 // the cache when `cached`).  Frames per request <= 64.

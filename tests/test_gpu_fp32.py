@@ -61,3 +61,25 @@ def test_fp32_attention_keys_of_no_weight(hd, tiles):
     q[:, ::hd] = -2.0
     cu = np.array([0, n], np.int32)
     check(q, k, v, heads, hd, cu, cu, dtype="f32", tag=f"fp32 no weight hd{hd} tiles {tiles}")
+
+
+def test_fp32_attention_beyond_one_launch():
+    """131073 queries of 4096 heads of one dim: more workgroups than the 2^32
+    threads of one launch hold.  Three keys, so that plain torch gives the
+    reference; |score| < 40 and |v| < 6, hence the same 1e-5."""
+    heads, n, kv = 4096, 131073, 3
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    q = torch.randn(n, heads, generator=gen, device="cuda")
+    k, v = (torch.randn(kv, heads, generator=gen, device="cuda") for _ in range(2))
+    o = torch.full((n, heads), float("nan"), device="cuda")
+    print(f"[attention] fp32 heads={heads} hd=1 n={n}", flush=True)
+    S.sphinx_varlen_attention(S.F32, heads, 1, q, heads, k, v, heads, o, np.array([0, n], np.int32),
+                              np.array([0, kv], np.int32))
+    worst = 0.0
+    for a in range(0, n, 16384):
+        s = q[a:a + 16384].double()[:, None] * k.double()
+        w = torch.exp2(s - s.amax(1, keepdim=True))
+        ref = (w * v.double()).sum(1) / w.sum(1)
+        worst = max(worst, float((o[a:a + 16384].double() - ref).abs().nan_to_num(nan=float("inf")).max()))
+    print(f"[attention beyond one launch] max_abs = {worst:.3e}", flush=True)
+    assert worst <= 1e-5
