@@ -748,7 +748,7 @@ sphinx_status refine_impl(const sphinx_model_desc* m, const sphinx_request* reqs
       else if (l % 2 == 0)  // spatial: within the frame
         SPHINX_TRY(launch_attention(dt, io, D, m->heads, m->head_dim, Sf, s));
       else  // temporal: across the request's frames at the same position
-        SPHINX_TRY(launch_attn_temporal(dt, T, io, D, m->heads, m->head_dim, I32(W.pos), cached, s));
+        SPHINX_TRY(launch_attn_temporal(dt, T, io, D, m->heads, m->head_dim, I32(W.pos), cached, cu_sel_host, s));
     }
     {
       Bracket br(SPHINX_K_GEMM_OUT, s);

@@ -35,6 +35,7 @@
 #include <type_traits>
 
 #include "kernels.hpp"
+#include "launch_rules.hpp"
 
 namespace sphinx {
 
@@ -1106,27 +1107,27 @@ __device__ __forceinline__ float head_sum(float x) {
 // them (readlane with the wave-uniform frame index).
 // Bound by the latency of the key loop: a selection is dense in some columns
 // and empty in others, and a wave per column that took its chunks of four in
-// turn left a few waves with four times the keys to walk.  So each chunk is a
-// wave (a column's waves are neighbours and find its rows in L1), and the next
-// key's row is loaded while one is used.  The order of a query's sums is the
-// same.  9677 of 32256 tokens in 14 frames at D 1024: 41.6 -> 29.4 us.
+// turn left a few waves with four times the keys to walk.  So the chunks of a
+// column are dealt to up to F / 4 neighbouring waves (temporal_waves in
+// launch_rules.hpp), which find its rows in L1, and the next key's row is loaded
+// while one is used.  The order of a query's sums is the same.  A column's first
+// chunk, the only one with work in a sparse column, goes to wave c mod chunks of
+// its waves: at a fixed place it fell on the same SIMD of every CU (64 frames of
+// 512 columns, 10 % selected, with the latent cache: 138 us, 94 so).
+// 9677 of 32256 tokens in 14 frames at D 1024: 41.6 -> 29.4 us.
 template <int DPL, int LPH>
 __global__ __launch_bounds__(256, DPL == 16 ? 3 : 4) void k_attn_temporal_lanes(ReqTable RT, AttnIO io, int D,
-                                                             const int32_t* __restrict__ pos, int cached, int ncols,
-                                                             int chunks) {
+                                                             const int32_t* __restrict__ pos, int cached,
+                                                             TemporalWaves P) {
   static_assert(DPL == 8 || DPL == 16, "8 or 16 dims per lane");
   constexpr int NV = DPL / 8;  // 16-byte vectors per lane and row
   const int lane = threadIdx.x & 63;
-  const int64_t wave = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  if (wave >= (int64_t)ncols * chunks) return;  // wave-uniform; the kernel has no barrier
-  int c = (int)(wave / chunks);
-  const int chunk = (int)(wave - (int64_t)c * chunks);
+  const uint32_t wave = blockIdx.x * 4u + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  if (wave >= P.first[RT.R]) return;  // wave-uniform; the kernel has no barrier
   int r = 0;
-  for (;; ++r) {
-    const int cols = (RT.h[r] >> 1) * (RT.w[r] >> 1);
-    if (c < cols || r + 1 == RT.R) break;
-    c -= cols;
-  }
+  while (r + 1 < RT.R && P.first[r + 1] <= wave) ++r;
+  const uint32_t chunks = P.chunks[r], col = (wave - P.first[r]) / chunks;
+  const int c = (int)col, chunk = (int)((wave - P.first[r] + col) % chunks);
   const int F = RT.frames[r];
   const int64_t tpf = (int64_t)(RT.h[r] >> 1) * (RT.w[r] >> 1);
   int p = -1, kr = 0;  // lane f < F: forwarded row of frame f's token, and its key row
@@ -1221,27 +1222,24 @@ __global__ __launch_bounds__(256, DPL == 16 ? 3 : 4) void k_attn_temporal_lanes(
         }
       }
     }
-    for (int i = 0; i < 4 * (chunks - 1); ++i) qm &= qm - 1;  // those of its other waves
+    for (uint32_t i = 0; i < 4 * (chunks - 1); ++i) qm &= qm - 1;  // those of its other waves
   }
 }
 }  // namespace
 
 hipError_t launch_attn_temporal(sphinx_dtype dt, const ReqTable& T, const AttnIO& io, int D, int heads,
-                                int head_dim, const int32_t* pos, bool cached, hipStream_t s) {
+                                int head_dim, const int32_t* pos, bool cached, const int32_t* cu_sel, hipStream_t s) {
   int64_t cols = 0;
   for (int r = 0; r < T.R; ++r) cols += (int64_t)(T.h[r] >> 1) * (T.w[r] >> 1);
   const int cf = cached ? 1 : 0;
   // lane-parallel kernel: rows of 64 x 16 or 64 x 8 dims, heads of 64 (of 4 or 8 lanes)
   if (dt == SPHINX_BF16 && head_dim == 64 && (D == 1024 || D == 512)) {
-    // waves per column: the longest request's frames in fours; one where that would pass the 2^32 threads of a launch
-    int chunks = 1;
-    for (int r = 0; r < T.R; ++r) chunks = std::max(chunks, (T.frames[r] + 3) / 4);
-    if (cols * chunks > ((int64_t)1 << 25)) chunks = 1;
-    const unsigned grid = (unsigned)((cols * chunks + 3) / 4);
+    const TemporalWaves P = temporal_waves(T.R, T.frames, T.h, T.w, cu_sel);
+    const unsigned grid = (P.first[T.R] + 3) / 4;
     if (D == 1024)
-      k_attn_temporal_lanes<16, 4><<<grid, 256, 0, s>>>(T, io, D, pos, cf, (int)cols, chunks);
+      k_attn_temporal_lanes<16, 4><<<grid, 256, 0, s>>>(T, io, D, pos, cf, P);
     else
-      k_attn_temporal_lanes<8, 8><<<grid, 256, 0, s>>>(T, io, D, pos, cf, (int)cols, chunks);
+      k_attn_temporal_lanes<8, 8><<<grid, 256, 0, s>>>(T, io, D, pos, cf, P);
     return hipGetLastError();
   }
   if (dt == SPHINX_BF16 && head_dim == 64)

@@ -114,9 +114,10 @@ hipError_t launch_attention(sphinx_dtype dt, const AttnIO& io, int D, int heads,
                             hipStream_t s);
 // Temporal attention of a factorised denoiser: pos[t] = forwarded row of token t
 // or -1; keys are the forwarded tokens of the column (or all of its frames from
-// the cache when `cached`).  Frames per request <= 64.
+// the cache when `cached`).  Frames per request <= 64.  cu_sel (host): prefix
+// sums of the requests' forwarded tokens.
 hipError_t launch_attn_temporal(sphinx_dtype dt, const ReqTable& T, const AttnIO& io, int D, int heads,
-                                int head_dim, const int32_t* pos, bool cached, hipStream_t s);
+                                int head_dim, const int32_t* pos, bool cached, const int32_t* cu_sel, hipStream_t s);
 // Per-frame counts of the forwarded rows and the token -> row map (rowwise.hip).
 hipError_t launch_frame_bounds(const ReqTable& T, const int32_t* idx, int n, int G, int32_t* first, hipStream_t s);
 hipError_t launch_pos_map(int64_t N, const int32_t* idx, int n, int32_t* pos, hipStream_t s);

@@ -122,8 +122,8 @@ def test_per_frame_grid():
 @pytest.mark.parametrize("D", [512, 1024])
 def test_factorised_lane_parallel_temporal(D):
     """bf16 rows of 512 or 1024 dims with heads of 64, where the temporal
-    blocks run lane-parallel (a wave per column, a head's dims over 8 or 4
-    lanes): two ragged requests, without and with the latent cache, end to end
+    blocks run lane-parallel (waves of four queries of a column, a head's dims
+    over 8 or 4 lanes): two ragged requests, without and with the latent cache, end to end
     and teacher-forced per step.  Every frame starts at t = 0.5 (amplification
     of per-step rounding at most 3.4; with starts up to 0.7 the D = 1024 run
     ends at 2.1e-2 on this and on the one-lane-per-query kernel alike, at the
@@ -149,6 +149,25 @@ def test_factorised_max_frames(case):
         wl = W.custom("fact_40_24_frames", FACT_BF16, [W.Request(40, 6, 6), W.Request(24, 4, 8)], [0.5, 0.5],
                       [0.3, 0.6], [3, 2])
     assert wl.G == 64
+    check(wl)
+    check(wl, period=2)
+
+
+@pytest.mark.parametrize("D", [512, 1024])
+def test_factorised_waves_per_column(D):
+    """Requests whose columns get 3, 2, 1 and 1 waves of the lane-parallel temporal
+    kernel in one launch: 33 frames of which two columns of 64 are selected whole
+    (a wave takes three of their nine chunks) and the others not at all, five
+    frames selected whole (two chunks, the second of one query), two frames, and
+    twenty sparse ones; against the oracle, without and with the latent cache,
+    where the full steps give every column of the first all nine."""
+    model = W.ModelCfg(D=D, heads=D // 64, head_dim=64, mlp=D, L=2, dtype="bf16", attention="factorised")
+    wl = W.custom(f"fact_waves_d{D}", model, [W.Request(33, 16, 16), W.Request(5, 6, 8), W.Request(2, 4, 4),
+                                              W.Request(20, 4, 4)], [0.5, 1.0, 0.5, 0.02], [0.4] * 4, [3] * 4)
+    u = wl.u[:wl.tok_offset[1]].reshape(33, 64)
+    u[:] = 0.0
+    u[:, [5, 42]] = 1.0
+    wl.thr[:33] = 0.5
     check(wl)
     check(wl, period=2)
 
