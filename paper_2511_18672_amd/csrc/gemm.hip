@@ -13,6 +13,7 @@
 #include <type_traits>
 
 #include "kernels.hpp"
+#include "launch_rules.hpp"
 
 namespace sphinx {
 
@@ -657,9 +658,6 @@ __device__ __forceinline__ void gemm_tall_body(const bf16* __restrict__ A, const
 // of panels four row tiles high, column by column inside a panel, so that the
 // tiles an XCD runs at a time share few rows of A and of W in its L2 (M 30925,
 // N 4096, K 1024: 268 us in plain order, 227 in panels).
-struct TallPlan {
-  int t1, n1, t2, n2;
-};
 template <int EPI, int BN>
 __global__ __launch_bounds__(512, 2) void k_gemm_tall(const bf16* __restrict__ A, const bf16* __restrict__ W,
                                                       const bf16* __restrict__ bias, int M, int N, int K, GemmEpi e,
@@ -875,74 +873,14 @@ int cu_count() {
   return c;
 }
 
-// Relative time of `tiles` workgroups at two per CU: whole rounds, plus half a
-// round for a last round that leaves every CU at most one tile (a lone tile
-// runs about twice as fast), else a whole one; `w` is the tile's cost in
-// 128-row-tile rounds.  Measured on the block GEMMs at M from 4.9k to 19.4k,
-// this picks the faster of the 128- and 192-row tiles or one within 1 %.
-double tile_rounds(int64_t tiles, int64_t slots, double w) {
-  const int64_t full = tiles / slots, rem = tiles % slots;
-  return w * ((double)full + (rem == 0 ? 0.0 : rem * 2 <= slots ? 0.5 : 1.0));
-}
-
-// Estimated times (us) of one round of tiles, for choosing between the tile
-// families: fitted on 64 block GEMMs of M 400 to 30925 at hidden sizes 512,
-// 1024 and 1152 (each in a stream of equal launches, so at power-limited
-// clocks); k is K in units of 1024, an h-row tile's cost grows with h.
-// Two 192x128 tiles per CU: 24 us at M 3226, N 3072, K 1024.
-double pair_round(int K, bool gated) {
-  const double k = K / 1024.0;
-  return 4.0 + 20.6 * k + (gated ? 6.0 : 0.0);
-}
-// One tall tile of h x bn per CU: 18.5, 26.9 and 29.8 us at 128, 224 and 256
-// rows of 256 columns, K 1024; gated 64 and 107 us at 128 and 256 rows, K 4096
-// (the residual's read and write is not hidden by another workgroup).
-double tall_round(int h, int bn, int K, bool gated) {
-  const double k = K / 1024.0, cols = h * bn / 256.0;
-  return (gated ? 4.0 : 1.4) + 5.2 * k + cols * ((gated ? 0.073 : 0.03) + 0.06 * k);
-}
-// The fastest plan of tall tiles by that estimate: equal row tiles, or whole
-// rounds of one height and one round of another for the rows left.
-struct TallChoice {
-  int bn = 0;
-  dma::TallPlan p{8, 0, 8, 0};
-  double us = 1e30;
-};
-TallChoice choose_tall(int epi, int M, int N, int K, int qcols, int cus) {
-  TallChoice best;
-  const bool gated = epi == EPI_GATED;
-  for (int bn : {256, 192}) {
-    if (N % bn != 0 || (epi == EPI_BIAS && qcols % bn != 0)) continue;
-    const int64_t nt = N / bn;
-    auto take = [&](const dma::TallPlan& p, double us) {
-      if (us < best.us) best = TallChoice{bn, p, us};
-    };
-    for (int t = 3; t <= 8; ++t) {
-      const int64_t n = (M + 32 * t - 1) / (32 * t);
-      take(dma::TallPlan{t, (int)n, t, 0}, (double)((n * nt + cus - 1) / cus) * tall_round(32 * t, bn, K, gated));
-    }
-    const int64_t per = cus / nt;  // row tiles of a round
-    if (per == 0) continue;
-    for (int t1 = 6; t1 <= 8; ++t1) {
-      const int64_t r = M / (32 * t1 * per), n1 = r * per, left = M - n1 * 32 * t1;
-      if (r == 0 || left == 0) continue;
-      const int64_t t2 = std::max<int64_t>(3, (left + 32 * per - 1) / (32 * per));
-      if (t2 > 8) continue;
-      take(dma::TallPlan{t1, (int)n1, (int)t2, (int)((left + 32 * t2 - 1) / (32 * t2))},
-           r * tall_round(32 * t1, bn, K, gated) + tall_round(32 * (int)t2, bn, K, gated));
-    }
-  }
-  return best;
-}
-
-void launch_tall(int epi, const TallChoice& c, const bf16* a, const bf16* w, const bf16* b, int M, int N, int K,
+void launch_tall(int epi, int bn, const TallPlan& p, const bf16* a, const bf16* w, const bf16* b, int M, int N, int K,
                  const GemmEpi& e, hipStream_t s) {
-  const int grid = (c.p.n1 + c.p.n2) * (N / c.bn);
+  const int grid = (p.n1 + p.n2) * (N / bn);
   auto go = [&](auto E, auto BN) {
-    dma::k_gemm_tall<decltype(E)::value, decltype(BN)::value><<<grid, 512, 0, s>>>(a, w, b, M, N, K, e, c.p);
+    dma::k_gemm_tall<decltype(E)::value, decltype(BN)::value><<<grid, 512, 0, s>>>(a, w, b, M, N, K, e, p);
   };
   auto by_bn = [&](auto E) {
-    if (c.bn == 256) go(E, std::integral_constant<int, 256>{});
+    if (bn == 256) go(E, std::integral_constant<int, 256>{});
     else go(E, std::integral_constant<int, 192>{});
   };
   if (epi == EPI_BIAS) by_bn(std::integral_constant<int, EPI_BIAS>{});
@@ -958,6 +896,15 @@ void launch_deep(int epi, int tiles, const bf16* a, const bf16* w, const bf16* b
   else if (epi == EPI_GELU) dma::k_gemm_dma_deep<EPI_GELU, NS, BM><<<tiles, 512, 0, s>>>(a, w, b, M, N, K, e);
   else dma::k_gemm_dma_deep<EPI_GATED, NS, BM><<<tiles, 512, 0, s>>>(a, w, b, M, N, K, e);
 }
+
+// 192- and 128-row tiles in one grid: p.nb and p.ns row tiles of each.
+template <bool WIDE>
+void launch_mix(int epi, int tiles, const GemmPlan& p, const bf16* a, const bf16* w, const bf16* b, int M, int N,
+                int K, const GemmEpi& e, hipStream_t s) {
+  if (epi == EPI_BIAS) dma::k_gemm_dma_mix<EPI_BIAS, WIDE><<<tiles, 256, 0, s>>>(a, w, b, M, N, K, e, p.nb, p.ns);
+  else if (epi == EPI_GELU) dma::k_gemm_dma_mix<EPI_GELU, WIDE><<<tiles, 256, 0, s>>>(a, w, b, M, N, K, e, p.nb, p.ns);
+  else dma::k_gemm_dma_mix<EPI_GATED, WIDE><<<tiles, 256, 0, s>>>(a, w, b, M, N, K, e, p.nb, p.ns);
+}
 }  // namespace
 
 hipError_t launch_gemm(int epi, sphinx_dtype dt, const void* A, const void* W, const void* bias, int M, int N, int K,
@@ -966,72 +913,25 @@ hipError_t launch_gemm(int epi, sphinx_dtype dt, const void* A, const void* W, c
     // the K loop takes two 64-deep steps at a time; the query scale is applied per 128-column tile
     if (K % 128 != 0 || N % 128 != 0 || (epi == EPI_BIAS && e.qcols % 128 != 0)) return hipErrorInvalidValue;
     const bf16 *a = (const bf16*)A, *w = (const bf16*)W, *b = (const bf16*)bias;
-    {
-      const int64_t nt = N / 128, slots = 2 * (int64_t)cu_count();
-      const int64_t t128 = nt * ((M + 127) / 128), t192 = nt * ((M + 191) / 192);
-      const int64_t cus = slots / 2, t256 = nt * ((M + 255) / 256), t64 = nt * ((M + 63) / 64);
-      // few tiles: the smallest row tile (128, 192 or 256 rows) whose tiles
-      // all fit on the CUs at once, one per CU with a deeper ring (128, 160
-      // or 144 KB of LDS; 64-row tiles 96 KB).  Tall tiles give nothing that a
-      // step shows here (MLP1 at M 1613: 18.7 us against 19.1 alone, the step
-      // within its noise)
-      if (t128 <= cus || t192 <= cus || t256 <= cus) {
-        // 64-row tiles where 128-row ones would leave more than half the CUs idle
-        if (t64 <= cus && 2 * t128 <= cus) launch_deep<4, 64>(epi, (int)t64, a, w, b, M, N, K, e, s);
-        else if (t128 <= cus) launch_deep<4, 128>(epi, (int)t128, a, w, b, M, N, K, e, s);
-        else if (t192 <= cus) launch_deep<4, 192>(epi, (int)t192, a, w, b, M, N, K, e, s);
-        else launch_deep<3, 256>(epi, (int)t256, a, w, b, M, N, K, e, s);
-        return hipGetLastError();
-      }
-      // mixed tiles: narrow N, 192-row tiles filling more than half of one round
-      int nb = -1, ns = 0;
-      if (nt <= 8 && slots % 16 == 0 && t192 * 2 > slots && t192 <= slots) {
-        const int per = (int)(slots / 8 / nt);  // slots per XCD and column tile
-        const int need = (M + 7) / 8;           // rows per XCD band
-        nb = std::max(0, (need - 128 * per + 63) / 64);
-        ns = per - nb;
-        if (nb * 2 > per) nb = -1;  // some CU would hold two 192-row tiles
-      }
-      // tall tiles where they are estimated faster than two 192- or 128-row
-      // tiles per CU; the narrow mix below takes three quarters of a round
-      // (M 9677: out-projection 27 us against 30 on tall tiles, MLP2 73 against 75)
-      const TallChoice tall = choose_tall(epi, M, N, K, e.qcols, (int)cus);
-      const double pair = pair_round(K, epi == EPI_GATED) *
-                          (nb >= 0 ? 0.75 : std::min(tile_rounds(t192, slots, 1.0), tile_rounds(t128, slots, 1.0 / 1.41)));
-      if (tall.us < pair) {
-        launch_tall(epi, tall, a, w, b, M, N, K, e, s);
-        return hipGetLastError();
-      }
-      // wide N needing more than three rounds of 192-row tiles: the last round
-      // all 128-row tiles (ns per column tile), 192-row tiles before it
-      if (nt > 8 && t192 > 3 * slots) {
-        const int ws = (int)(slots / nt);
-        const int wb = (M - 128 * ws + 191) / 192;
-        if (ws > 0 && wb > 0) {
-          const int grid = (wb + ws) * (int)nt;
-          if (epi == EPI_BIAS) dma::k_gemm_dma_mix<EPI_BIAS, true><<<grid, 256, 0, s>>>(a, w, b, M, N, K, e, wb, ws);
-          else if (epi == EPI_GELU) dma::k_gemm_dma_mix<EPI_GELU, true><<<grid, 256, 0, s>>>(a, w, b, M, N, K, e, wb, ws);
-          else dma::k_gemm_dma_mix<EPI_GATED, true><<<grid, 256, 0, s>>>(a, w, b, M, N, K, e, wb, ws);
-          return hipGetLastError();
-        }
-      }
-      if (nb >= 0) {
-        const int grid = 8 * (nb + ns) * (int)nt;
-        if (epi == EPI_BIAS) dma::k_gemm_dma_mix<EPI_BIAS, false><<<grid, 256, 0, s>>>(a, w, b, M, N, K, e, nb, ns);
-        else if (epi == EPI_GELU) dma::k_gemm_dma_mix<EPI_GELU, false><<<grid, 256, 0, s>>>(a, w, b, M, N, K, e, nb, ns);
-        else dma::k_gemm_dma_mix<EPI_GATED, false><<<grid, 256, 0, s>>>(a, w, b, M, N, K, e, nb, ns);
-      } else if (tile_rounds(t192, slots, 1.41) < tile_rounds(t128, slots, 1.0)) {
-        // a 192-row tile does 1.5x the work of a 128-row one in 1.41x the time
-        const int tiles = (int)t192;
-        if (epi == EPI_BIAS) dma::k_gemm_dma192_bias<<<tiles, 256, 0, s>>>(a, w, b, M, N, K, e);
-        else if (epi == EPI_GELU) dma::k_gemm_dma192_gelu<<<tiles, 256, 0, s>>>(a, w, b, M, N, K, e);
-        else dma::k_gemm_dma192_gated<<<tiles, 256, 0, s>>>(a, w, b, M, N, K, e);
-      } else {
-        const int tiles = (int)t128;
-        if (epi == EPI_BIAS) dma::k_gemm_dma_bias<<<tiles, 256, 0, s>>>(a, w, b, M, N, K, e);
-        else if (epi == EPI_GELU) dma::k_gemm_dma_gelu<<<tiles, 256, 0, s>>>(a, w, b, M, N, K, e);
-        else dma::k_gemm_dma_gated<<<tiles, 256, 0, s>>>(a, w, b, M, N, K, e);
-      }
+    const GemmPlan p = plan_gemm(epi == EPI_GATED, epi == EPI_BIAS ? e.qcols : 0, M, N, K, cu_count());
+    const int nt = N / 128, t128 = nt * ((M + 127) / 128), t192 = nt * ((M + 191) / 192);
+    switch (p.tiles) {
+      case kDeep64: launch_deep<4, 64>(epi, nt * ((M + 63) / 64), a, w, b, M, N, K, e, s); break;
+      case kDeep128: launch_deep<4, 128>(epi, t128, a, w, b, M, N, K, e, s); break;
+      case kDeep192: launch_deep<4, 192>(epi, t192, a, w, b, M, N, K, e, s); break;
+      case kDeep256: launch_deep<3, 256>(epi, nt * ((M + 255) / 256), a, w, b, M, N, K, e, s); break;
+      case kTall: launch_tall(epi, p.bn, p.tall, a, w, b, M, N, K, e, s); break;
+      case kMixWide: launch_mix<true>(epi, (p.nb + p.ns) * nt, p, a, w, b, M, N, K, e, s); break;
+      case kMixNarrow: launch_mix<false>(epi, 8 * (p.nb + p.ns) * nt, p, a, w, b, M, N, K, e, s); break;
+      case kPair192:
+        if (epi == EPI_BIAS) dma::k_gemm_dma192_bias<<<t192, 256, 0, s>>>(a, w, b, M, N, K, e);
+        else if (epi == EPI_GELU) dma::k_gemm_dma192_gelu<<<t192, 256, 0, s>>>(a, w, b, M, N, K, e);
+        else dma::k_gemm_dma192_gated<<<t192, 256, 0, s>>>(a, w, b, M, N, K, e);
+        break;
+      default:
+        if (epi == EPI_BIAS) dma::k_gemm_dma_bias<<<t128, 256, 0, s>>>(a, w, b, M, N, K, e);
+        else if (epi == EPI_GELU) dma::k_gemm_dma_gelu<<<t128, 256, 0, s>>>(a, w, b, M, N, K, e);
+        else dma::k_gemm_dma_gated<<<t128, 256, 0, s>>>(a, w, b, M, N, K, e);
     }
   } else {
     if (K % kF32BK != 0 || N % kF32BN != 0 || (epi == EPI_BIAS && e.qcols % kF32BN != 0)) return hipErrorInvalidValue;
