@@ -35,7 +35,8 @@ constexpr int kHaloX = 8;                    // 1 (Laplacian) + 4 (9-wide window
 constexpr int kWinL = 9, kWinV = 5;          // rows of the variance window and of the box
 constexpr int kQuantPix = 4096;              // pixels per k_front_quant workgroup
 constexpr int kHistCopies = 16;
-constexpr int kSplitTiles = 512;             // tiles up to which four waves share one
+constexpr int kSplit4Tiles = 512;            // tiles up to which four waves share one,
+constexpr int kSplit2Tiles = 1280;           // and up to which two do
 constexpr int kFewTiles = 512;               // tiles per frame up to which k_front_quant takes their min/max itself
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return min(max(v, lo), hi); }
@@ -97,7 +98,11 @@ __device__ __forceinline__ void luma4(const Raw& q, int (&y)[4]) {
 // where the tiles would leave most of the 1024 SIMDs idle (up to 512 of them)
 // four waves walk 16 rows for 4 each, for 1.7 times the work.  A whole call on
 // small requests (a few hundred tokens on): 32 us with one wave, 24 with four (25 with
-// the tiles in LDS described below).
+// the tiles in LDS described below).  Two waves walk 20 rows for 8 each (1.4 times
+// the work) and their 29 KB of ring lets the 256 CUs hold 1280 such workgroups at
+// once, so up to there they save a third of a lone wave's rows: 300 frames of
+// 64 x 64 in 1200 tiles 43.8 us (45.1 with one wave, 43.0 with the tiles in LDS),
+// 8 frames of 512 x 512 in 768 tiles 40.6 (42.5, 58.1).
 // A 64 x 16 tile per workgroup with every stage in LDS took 100 us for
 // 14 frames of 576 x 1024; this takes 35 us.
 template <int NW>
@@ -587,8 +592,10 @@ hipError_t launch_front(const ReqTable& T, int G, const uint8_t* rgb, const floa
   uint8_t* inv = base;
   base += a256((size_t)pixels);
   double* wm = reinterpret_cast<double*>(base);
-  if (tiles <= kSplitTiles)
+  if (tiles <= kSplit4Tiles)
     k_front_var<4><<<tiles, 4 * kWave, 0, s>>>(T, F, rgb, part, wm, hist);
+  else if (tiles <= kSplit2Tiles)
+    k_front_var<2><<<tiles, 2 * kWave, 0, s>>>(T, F, rgb, part, wm, hist);
   else
     k_front_var<1><<<tiles, kWave, 0, s>>>(T, F, rgb, part, wm, hist);
   bool large = false;

@@ -152,12 +152,14 @@ def test_frontend_many_tiles(h):
     check(reqs, rgb, [np.ones_like(o) for o in opac], tag=f"tiles {h // 2}")
 
 
+@pytest.mark.parametrize("tiles", [520, 1290])
 @pytest.mark.parametrize("w", [28, 62, 90])
-def test_frontend_many_frames(w):
-    """More than 512 tiles in all, where one wave takes a whole tile, at widths
-    with one and three tiles across (the tests above take four waves)."""
-    frames = 520 // (2 * -(-8 * w // 240)) + 1
+def test_frontend_many_frames(w, tiles):
+    """More than 512 tiles in all, where two waves share a tile, and more than
+    1280, where one takes it whole, at widths with one to three tiles across
+    (the tests above take four waves)."""
+    frames = tiles // (2 * -(-8 * w // 240)) + 1
     reqs = [W.Request(frames, 4, w)]
     rng = np.random.default_rng(w)
     rgb = [rng.integers(0, 256, (frames, 32, 8 * w, 3), dtype=np.uint8)]
-    check(reqs, rgb, [np.ones((frames, 32, 8 * w), np.float32)], tag=f"many frames {w}")
+    check(reqs, rgb, [np.ones((frames, 32, 8 * w), np.float32)], tag=f"many frames {w} {tiles}")
