@@ -23,11 +23,16 @@ namespace {
 //  * Block tile 128x128x64, 4 waves in 2x2, each a 64x64 tile of 4x4
 //    v_mfma_f32_16x16x32_bf16; two workgroups per CU.  That form draws less
 //    power than the 32x32x16 one at the same work (register-only loops on random
-//    operands run at 2050 against 1790 TFLOP/s), and long runs are power-limited;
-//    eight-wave tiles of small selections, bound by latency, take the 32x32x16
-//    form with its smaller number of instructions (QKV at M 1613: 16.5 us against
-//    17.5).  Both add the products of a row in ascending k and round alike
-//    (bit-identical on every shape measured).
+//    operands run at 2050 against 1790 TFLOP/s), and long runs are power-limited.
+//    In these kernels it gives up to 4 % (M 10816, D 1152, QKV 101.4 -> 97.0 us;
+//    M 23712, D 512, QKV 44.7 -> 43.2, D 640, MLP2 84.7 -> 81.4), at most sizes
+//    nothing that shows.  Eight-wave tiles of small selections, bound by latency,
+//    take the 32x32x16 form with its smaller number of instructions (QKV at M
+//    1613: 16.5 us against 17.5).  Both add the products of a row in ascending k.
+//    That they also round alike inside an instruction is measured, not given by
+//    their definition: 67 million outputs of K 32 to 4096 from operands of like
+//    size, of exponents over 2^+-30, with cancelling pairs, with subnormal
+//    products and with overflow are the same to the bit.
 //  * Operand tiles are unpadded 128-byte rows (A rows, then W rows, of one
 //    64-wide K step); chunk c of row r sits at c ^ ((r >> 1) & 7), which spreads
 //    the 16 rows of one ds_read_b128 pass (same chunk) over all 64 LDS banks.
@@ -47,8 +52,9 @@ namespace {
 //    k-step's MFMAs.  Barriers carry no memory fence: each wave waits for its
 //    own copies (vmcnt) and LDS reads (lgkmcnt) first.
 //  * Every output starts at its bias and accumulates its k-steps in ascending
-//    k, whatever the tile shape, so all variants give bit-identical
-//    results.
+//    k, whatever the tile shape; with the two MFMA forms rounding alike, all
+//    variants give bit-identical results (every one is compared in
+//    tests/test_gpu_gemm_tiles.py), so packed and separate requests do too.
 //  * A 192-row variant (wave tiles 96x64, 80 KB of LDS, epilogue staged one
 //    wave row at a time) is launched where its smaller tile count packs into
 //    fewer rounds of two workgroups per CU; same results.
@@ -436,8 +442,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm_dma_mix(const bf16* __restrict_
 // workgroup per CU.
 //  * Waves in 2x4, each 16 TI x BN/4 outputs; two stages of 64-deep K steps.
 //  * The chip is power-limited on these kernels (1.7-1.8 GHz in a stream of
-//    them), so a tile's worth is its bytes moved per FLOP: 256x256 copies 2/3 of
-//    the bytes of 192x128 from L2 to LDS and reads 4/5 of the fragment bytes.
+//    them), so a tile's worth is its bytes moved per FLOP: 256x256 copies 3/5 of
+//    the bytes of 192x128 from L2 to LDS and reads 9/10 of the fragment bytes.
 //    Rows of 128 bytes matter as well: half-line (64-byte) copies ran at half
 //    the L2 rate (1256 instead of 1115 cycles per 1024 of MFMA work).
 //  * Row i of a k-step (TJ MFMAs on fa[i]) is followed by the read of the next
@@ -453,7 +459,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_dma_mix(const bf16* __restrict_
 // Against the two-per-CU tiles, streams of equal launches: M 9677, K 1024, N 3072
 // 65 -> 58 us and N 4096 88 -> 79; M 30925, N 1024, K 4096 (gated) 301 -> 241.
 // Every output starts at its bias and adds its products in ascending k, as in
-// the other tiles: same results.
+// the other tiles: same results, as described there.
 template <int EPI, int TI, int BN>
 __device__ __forceinline__ void gemm_tall_body(const bf16* __restrict__ A, const bf16* __restrict__ W,
                                                const bf16* __restrict__ bias, int M, int K, const GemmEpi& e,

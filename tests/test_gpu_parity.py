@@ -373,10 +373,12 @@ def test_headline_width_few_tile_gemms(rho):
 
 
 def test_few_tile_gemms_match_packed():
-    """The deep-ring GEMM tiles give bit-identical results to the two-workgroup
-    tiles: three headline-shape requests (1613, 4838 and 6451 selected tokens)
-    each alone run on the deep-ring kernels, and packed into one launch (12902
-    rows) on the two-workgroup kernels."""
+    """The deep-ring GEMM tiles give bit-identical results to the tall ones: three
+    headline-shape requests (1613, 4838 and 6451 selected tokens), whose
+    out-projections and MLP2, and at 1613 all four GEMMs, run alone on the
+    deep-ring kernels, packed into one launch (12902 rows) that runs them all on
+    tall tiles of 160, 192 and 224 rows.  The tiles of two workgroups per CU are
+    in test_gemm_kernels_round_alike."""
     model = W.ModelCfg(D=1024, heads=16, head_dim=64, mlp=4096, L=1, dtype="bf16")
     req = W.Request(14, 72, 128)
     wl = W.custom("few_tile_packed", model, [req, req, req], [0.05, 0.15, 0.2], [0.5, 0.5, 0.5], [25, 25, 25])
@@ -405,6 +407,7 @@ def test_headline_full_depth_properties():
 def _packed_vs_separate(wl):
     R, _, _ = run_gpu(wl, steps=1)
     packed = R.state.cpu().numpy()
+    assert np.isfinite(packed).all()
     del R
     worst = 0.0
     for r, q in enumerate(wl.requests):
@@ -416,6 +419,7 @@ def _packed_vs_separate(wl):
                          eps=wl.eps[16 * wl.tok_offset[r]:16 * wl.tok_offset[r + 1]], weights=wl.weights)
         Rr, _, _ = run_gpu(one, steps=1)
         sep = Rr.state.cpu().numpy()
+        assert np.isfinite(sep).all()
         worst = max(worst, float(np.abs(sep - packed[16 * wl.tok_offset[r]:16 * wl.tok_offset[r + 1]]).max()))
         del Rr
     return worst
