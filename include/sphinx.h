@@ -400,7 +400,7 @@ sphinx_status sphinx_scatter_masked(const sphinx_request* reqs, int32_t R, const
  *          pixel is 8 x 8 image pixels, a token 2 x 2 latent pixels).
  * ------------------------------------------------------------------------ */
 
-/* Workspace bytes of sphinx_mask_frontend (about one byte per image pixel). */
+/* Workspace bytes of sphinx_mask_frontend (about nine bytes per image pixel). */
 sphinx_status sphinx_mask_frontend_workspace_bytes(const sphinx_request* reqs, int32_t R, size_t* bytes);
 
 /* rgb: dev uint8, per request [frames][8h][8w][3] (interleaved RGB, rows of

@@ -40,7 +40,7 @@ typedef SPHINX_ENUM {
   SPHINX_K_FINAL,      /* final LayerNorm + projection + DDIM update */
   SPHINX_K_SCATTER,
   SPHINX_K_KV_STORE,   /* latent cache store of the forwarded rows' keys and values */
-  SPHINX_K_FRONTEND,   /* mask front-end (five kernels, one bracket) */
+  SPHINX_K_FRONTEND,   /* mask front-end (four or five kernels, one bracket) */
   SPHINX_K_COUNT
 } sphinx_kernel_class;
 
