@@ -441,9 +441,11 @@ __global__ __launch_bounds__(256, 2) void k_gemm_dma_mix(const bf16* __restrict_
 // Tall tiles: 32 TI rows (TI 3 .. 8) x BN columns (192 or 256), one eight-wave
 // workgroup per CU.
 //  * Waves in 2x4, each 16 TI x BN/4 outputs; two stages of 64-deep K steps.
-//  * The chip is power-limited on these kernels (1.7-1.8 GHz in a stream of
-//    them), so a tile's worth is its bytes moved per FLOP: 256x256 copies 3/5 of
-//    the bytes of 192x128 from L2 to LDS and reads 9/10 of the fragment bytes.
+//  * A tile's worth is its bytes moved per FLOP: 256x256 copies 3/5 of the bytes
+//    of 192x128 from L2 to LDS and reads 9/10 of the fragment bytes.  In the
+//    headline step these kernels issue MFMAs at 44 % (QKV) and 43 % (MLP1) of the
+//    register-only rate at about 2.4 GHz; in streams of equal launches the clock
+//    falls (1.7-1.8 GHz), and fewer bytes help there as well.
 //    Rows of 128 bytes matter as well: half-line (64-byte) copies ran at half
 //    the L2 rate (1256 instead of 1115 cycles per 1024 of MFMA work).
 //  * Row i of a k-step (TJ MFMAs on fa[i]) is followed by the read of the next

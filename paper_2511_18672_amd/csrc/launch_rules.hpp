@@ -86,16 +86,16 @@ inline double tall_round(int h, int bn, int K, bool gated) {
 // about 250 launches lose more than 2 %, all three rounds of 192x256 (D 2048, M 6080,
 // QKV: 144 us, 130; D 1536, M 12096, N 3072: 116, 108), which elsewhere gain 4 to 14 %.
 //
-// Gated launches of more than one round need more: later rounds run
-// power-limited, which costs small tiles more (M 10816, D 1536, K 6144: 232 us
-// on two rounds of 128x256, 202 on two tiles per CU; but M 31680: 525 on three
-// rounds of 256x256, 646).  Times of whole launches, fitted on the out-projection
+// Gated launches of more than one round need more: later rounds take longer than
+// the first, by more the smaller the tile (M 10816, D 1536, K 6144: 232 us on two
+// rounds of 128x256, 202 on two tiles per CU; but M 31680: 525 on three rounds of
+// 256x256, 646).  Times of whole launches, fitted on the out-projection
 // and MLP2 of those steps (5 and 7 % rms).  Tiles of 192 columns gain nothing in
 // two or three rounds at all (M 27552, D 768, K 3072: 163 us, 149; M 31680,
 // D 1152, K 4608: 370, 352), but in five they do (M 31680, D 1920, K 7680: 926,
 // 1133).  So over 173 gated launches the choice costs 0.3 % against the faster
-// family on average and 2.5 % at most against two tiles per CU; the rates of one
-// round alone cost up to 14 %.
+// family on average and 2.5 % at most against two tiles per CU (on 42 launches
+// measured afterwards, 4 %); the rates of one round alone cost up to 14 %.
 inline double gated_tall_time(int bn, double r1, int t1, double r2, int t2, int K) {
   const double k = K / 1024.0;
   auto round = [&](int t) { return 1.6 * k - 5.4 + t * bn / 8.0 * (0.109 + 0.08 * k); };
